@@ -7,6 +7,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <mutex>
@@ -102,6 +103,11 @@ struct nmt_model {
   // are bound by memory traffic, which fp32 table rows and projections
   // would raise.
   bool precomp = false;
+  // the products but the vocabulary's run on the fp16 matrix cores, weights
+  // as two halves (Packed::sp; see split_weights), and the embeddings' scales
+  // as A operands of the tables and the encoder
+  bool split = false;
+  int emb_scale_src = 0, emb_scale_tgt = 0;
   Packed g1x, roy, cpw;
   int cpw_ld = 0;  // columns of a projection row: 3H + E, padded to the large tile
   float *tab_x = nullptr, *tab_y = nullptr;
@@ -298,10 +304,100 @@ hipError_t word_tables(nmt_model* m, hipStream_t st) {
   hipError_t e = m->mem.alloc((void**)&m->tab_x, (size_t)V * 3 * H * 4);
   if (e == hipSuccess) e = m->mem.alloc((void**)&m->tab_y, (size_t)V * E * 4);
   const AOperand A = make_a(V, {emb_seg(m, m->emb_tgt, nullptr, V)});
-  if (e == hipSuccess)
-    e = launch_gemm_plain(Tile::Large, A, m->g1x, PlainEpi{m->tab_x, 3 * H, nullptr, 3 * H, 0, nullptr, 1}, st);
-  if (e == hipSuccess)
-    e = launch_gemm_plain(Tile::Large, A, m->roy, PlainEpi{m->tab_y, E, nullptr, E, 0, nullptr, 1}, st);
+  auto table = [&](const Packed& W, float* out, int N) {
+    const PlainEpi ep{out, N, nullptr, N, 0, nullptr, 1};
+    return m->split ? launch_plain_sp(SpA{(const float*)m->emb_tgt, nullptr, 0, E, E, V, m->emb_scale_tgt, 0.f}, W.sp,
+                                      ep, m->cus, st)
+                    : launch_gemm_plain(Tile::Large, A, W, ep, st);
+  };
+  if (e == hipSuccess) e = table(m->g1x, m->tab_x, 3 * H);
+  if (e == hipSuccess) e = table(m->roy, m->tab_y, E);
+  return e;
+}
+
+// An fp32 model's weights as halves for the fp16 matrix cores (split.hip),
+// packed from the fp32 ones: the output weights (Packed::sp of out), and,
+// for precomp models of at least kSplitMinH units, those of every other
+// product (split = true).  Either is left out, and the fp32 MFMA kernels
+// kept, where the range of some matrix, embedding table or the output bias
+// does not allow it.  Waits for the stream.
+hipError_t split_weights(nmt_model* m, hipStream_t st) {
+  const nmt_dims& d = m->dims;
+  struct Item {
+    Packed* W;
+    int K, gru_hb;
+  };
+  const int hb = gru_hb(false);
+  std::vector<Item> all = {{&m->enc_in, d.E, 0},     {&m->enc_U[0], d.H, hb},   {&m->enc_U[1], d.H, hb},
+                           {&m->att_Wc, 2 * d.H, 0}, {&m->init_W, 2 * d.H, 0},  {&m->g1, d.H, hb},
+                           {&m->att_Wq, d.H, 0},     {&m->g2, d.H, hb},         {&m->ro, d.H, 0},
+                           {&m->g1x, d.E, 0},        {&m->roy, d.E, 0},         {&m->cpw, 2 * d.H, 0}};
+  const Item out = {&m->out, d.E, 0};
+  m->split = false;
+  m->out.sp = SplitW{};
+  for (const Item& it : all) it.W->sp = SplitW{};
+  if (m->bf16) return hipSuccess;
+  size_t n = std::max(std::max(d.V_src, d.V), (int)m->out.Npad);
+  for (const Item& it : all) n = std::max(n, (size_t)it.W->Npad);
+  uint32_t* dev = nullptr;
+  hipError_t e = device_malloc((void**)&dev, n * 4);
+  if (e != hipSuccess) return e;
+  std::vector<uint32_t> host;
+  auto fetch = [&](size_t count) {
+    host.resize(count);
+    if (e == hipSuccess) e = hipMemcpyAsync(host.data(), dev, count * 4, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    return e == hipSuccess;
+  };
+  // the matrix's scale and packed size; false where it keeps the fp32 form
+  auto plan = [&](const Item& it, bool vocab) {
+    SplitW& sp = it.W->sp;
+    sp.K = it.K;
+    sp.steps = split_steps(it.K, vocab);
+    sp.blocks = it.gru_hb ? 3 * (int64_t)ceil_div(d.H, 32) : it.W->Npad / 32;
+    if (e == hipSuccess) e = launch_magnitudes(*it.W, it.K, dev, st);
+    sp.scale = fetch((size_t)it.W->Npad) ? split_scale(host) : kNoSplit;
+    return sp.scale != kNoSplit &&
+           (vocab ? split_vocab_fits(it.K, sp.blocks) : split_bytes(sp.blocks, sp.steps) < ((int64_t)1 << 31));
+  };
+  auto pack = [&](const Item& it) {
+    SplitW& sp = it.W->sp;
+    if (e == hipSuccess) e = m->mem.alloc(&sp.d, (size_t)split_bytes(sp.blocks, sp.steps));
+    if (e == hipSuccess) e = launch_split_pack(*it.W, it.K, sp.steps, sp.blocks, it.gru_hb, sp.scale, sp.d, st);
+  };
+  bool fits = plan(out, true);
+  if (fits) {  // biases that are finite must stay so in the accumulators' units
+    const int bias_scale = m->out.sp.scale + kSplitReadout;
+    if (e == hipSuccess) e = launch_scaled_bias(m->out, 0, m->out.Npad, (float*)dev, st);
+    if (fetch((size_t)m->out.Npad))
+      for (uint32_t u : host) {
+        float b;
+        memcpy(&b, &u, 4);
+        if (std::isfinite(b) && !std::isfinite(std::ldexp(b, bias_scale))) fits = false;
+      }
+    if (e == hipSuccess && fits) {
+      SplitW& sp = m->out.sp;
+      pack(out);
+      if (e == hipSuccess) e = m->mem.alloc((void**)&sp.bias, (size_t)sp.blocks * 32 * 4);
+      if (e == hipSuccess) e = launch_scaled_bias(m->out, bias_scale, sp.blocks * 32, sp.bias, st);
+    }
+  }
+  if (!fits) m->out.sp = SplitW{};
+  fits = e == hipSuccess && m->precomp && d.H >= kSplitMinH;
+  for (const Item& it : all) fits = fits && plan(it, false);
+  for (int i = 0; i < 2 && fits && e == hipSuccess; ++i) {
+    const int rows = i ? d.V : d.V_src;
+    e = launch_row_magnitudes((const float*)(i ? m->emb_tgt : m->emb_src), rows, d.E, dev, st);
+    const int s = fetch((size_t)rows) ? split_scale(host) : kNoSplit;
+    (i ? m->emb_scale_tgt : m->emb_scale_src) = s;
+    fits = s != kNoSplit;
+  }
+  if (fits)
+    for (const Item& it : all) pack(it);
+  else
+    for (const Item& it : all) it.W->sp = SplitW{};
+  m->split = fits && e == hipSuccess;
+  device_free(dev);
   return e;
 }
 
@@ -358,10 +454,15 @@ WsLayout ws_layout(const nmt_model* m, int64_t B) {
   off += al((size_t)B * d.A * 4);
   L.t = off;
   off += al((size_t)B * d.E * 4);
-  L.vtm = vocab_tm((int)B, m->dims.V, m->bf16, m->out.Kpad, m->dims.E, m->out.nbias, m->cus);
-  L.nS = vocab_slices((int)B, m->dims.V, m->bf16, m->cus, L.vtm);
+  L.vtm = vocab_tm((int)B, d.V, m->bf16, m->out.Kpad, d.E, m->out.nbias, m->cus);
+  L.nS = vocab_slices((int)B, d.V, m->bf16, m->cus, L.vtm);
+  int part_slices = L.nS;
+  if (m->out.sp.d) {
+    split_vocab_shape((int)B, d.V, m->cus, &L.vtm, &L.nS);
+    part_slices = std::max(part_slices, L.nS);
+  }
   L.part = off;
-  off += al((size_t)B * L.nS * sizeof(float2));
+  off += al((size_t)B * part_slices * sizeof(float2));
   // The query GEMM splits its K where its tiles fit in one round of the CUs
   // (a forest's levels, the phrase loop, B = 1000 at A = 1024), the attention
   // adding the split sums as it loads the query: ruen_b1000 query 27.1 ->
@@ -399,6 +500,11 @@ WsLayout ws_layout(const nmt_model* m, int64_t B) {
     off = end > off ? end : off;
   }
   L.total = off;
+  // Split weights share K between the waves of a tile and use no partial
+  // sums; the bytes stay those of the fp32 MFMA form, so that a workspace
+  // serves every model of these sizes whichever form its weights allow (an
+  // average can come out in another form than its members).
+  if (m->split) L.ks_q = L.ks_ro = L.ks_g1 = L.ks_g2 = 1;
   return L;
 }
 
@@ -406,6 +512,7 @@ WsLayout ws_layout(const nmt_model* m, int64_t B) {
 // (S <= 64: 16 column tiles x 2 directions), so each step's K chunks are
 // split until the blocks cover the CUs, at least two chunks per split.
 int encoder_ksplit(const nmt_model* m, int S) {
+  if (m->split) return 1;
   const int base = ceil_div(S, kGruSmallTM) * ceil_div(m->dims.H, gru_hb(m->bf16)) * 2;
   const int nc = ceil_div(m->dims.H, m->kc);
   int ks = m->cus / base;
@@ -460,12 +567,14 @@ hipError_t source_keys(nmt_model* m, nmt_source* src, hipStream_t st) {
   const int C = 2 * d.H;
   AOperand A = make_a(src->S * src->Tpad, {make_seg(src->ctx, C, C, 0, m->kc)});
   PlainEpi ep{src->pctx, d.A, m->att_b, d.A, 0, src->len, src->Tpad};
-  hipError_t e = launch_gemm_plain(Tile::Large, A, m->att_Wc, ep, st);
+  const SpA As{src->ctx, nullptr, 0, C, C, src->S * src->Tpad, kSplitState, 0.f};
+  hipError_t e = m->split ? launch_plain_sp(As, m->att_Wc.sp, ep, m->cus, st)
+                          : launch_gemm_plain(Tile::Large, A, m->att_Wc, ep, st);
   if (e == hipSuccess) e = launch_key_factors(src->S, src->Tpad, d.A, src->pctx, src->kfac, src->kbig, st);
   if (e == hipSuccess && m->precomp) {
     // the context's products, projected per position (zeros past the length)
     PlainEpi pe{src->cproj, m->cpw_ld, nullptr, m->cpw_ld, 0, src->len, src->Tpad};
-    e = launch_gemm_plain(Tile::Large, A, m->cpw, pe, st);
+    e = m->split ? launch_plain_sp(As, m->cpw.sp, pe, m->cus, st) : launch_gemm_plain(Tile::Large, A, m->cpw, pe, st);
   }
   return e;
 }
@@ -656,6 +765,7 @@ nmt_status nmt_model_create(const nmt_dims* dims, const nmt_weights* w, nmt_mode
     m->out.Krows = E;
     m->out.nbias = nb;
   }
+  if (e == hipSuccess) step(split_weights(m, nullptr));
   if (e == hipSuccess && m->precomp) step(word_tables(m, nullptr));
   step(m->mem.alloc((void**)&m->err, sizeof(int)));
   if (e == hipSuccess) step(hipMemset(m->err, 0, sizeof(int)));
@@ -705,7 +815,10 @@ nmt_status nmt_encode(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* d_sr
   if (e == hipSuccess) {
     AOperand A = make_a((int)rows, {emb_seg(m, m->emb_src, d_src_ids, d.V_src)});
     PlainEpi ep{Xp, 6 * H, m->enc_in_b, 6 * H, 0, nullptr, 1};
-    e = launch_gemm_plain(Tile::Large, A, m->enc_in, ep, st);
+    e = m->split ? launch_plain_sp(SpA{(const float*)m->emb_src, d_src_ids, d.V_src, E, E, (int)rows, m->emb_scale_src,
+                                       0.f},
+                                   m->enc_in.sp, ep, m->cus, st)
+                 : launch_gemm_plain(Tile::Large, A, m->enc_in, ep, st);
   }
   // The recurrence: step t runs the forward direction at position t and the
   // backward direction at position Tpad-1-t in one launch.  Positions at or
@@ -726,8 +839,20 @@ nmt_status nmt_encode(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* d_sr
       g.ep = GruEpi{hprev, ldc, nullptr, 0, Xp + (int64_t)pos * 6 * H + dir * 3 * H, ldx, m->enc_bias.brz, m->enc_bias.bni,
                     m->enc_bias.bns, src->ctx + (int64_t)pos * C + dir * H, ldc, src->len, pos, H};
     }
-    const bool split = src->enc_ks > 1 && p[0].A.nseg > 0 && p[1].A.nseg > 0;
-    e = split ? launch_gemm_gru_split(p, 2, H, m->bf16, src->enc_ks, src->gru_part, S, kGruSmallTM, st)
+    if (m->split) {
+      SpA a[2];
+      const SplitW* w[2];
+      GruEpi ep[2];
+      for (int dir = 0; dir < 2; ++dir) {
+        ep[dir] = p[dir].ep;
+        w[dir] = &m->enc_U[dir].sp;
+        a[dir] = SpA{ep[dir].h, nullptr, 0, ldc, ep[dir].h ? H : 0, S, kSplitState, 0.f};
+      }
+      e = launch_gru_sp(a, w, ep, 2, m->cus, st);
+      continue;
+    }
+    const bool ksplit = src->enc_ks > 1 && p[0].A.nseg > 0 && p[1].A.nseg > 0;
+    e = ksplit ? launch_gemm_gru_split(p, 2, H, m->bf16, src->enc_ks, src->gru_part, S, kGruSmallTM, st)
               : launch_gemm_gru(p, 2, H, m->bf16, m->cus, st);
   }
   if (e == hipSuccess) e = source_keys(m, src, st);
@@ -737,7 +862,8 @@ nmt_status nmt_encode(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* d_sr
     if (e == hipSuccess) {
       AOperand A = make_a(S, {make_seg(mean, C, C, 0, m->kc)});
       PlainEpi ep{d_s0_out, H, m->init_b, H, 1, nullptr, 1};
-      e = launch_gemm_plain(Tile::Small, A, m->init_W, ep, st);
+      e = m->split ? launch_plain_sp(SpA{mean, nullptr, 0, C, C, S, kSplitState, 0.f}, m->init_W.sp, ep, m->cus, st)
+                   : launch_gemm_plain(Tile::Small, A, m->init_W, ep, st);
     }
   }
   if (e != hipSuccess) {
@@ -889,14 +1015,20 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
     g1.ep.xrows = V;
   }
   float* gpart = (float*)(ws + L.gpart);
-  auto run_gru = [&](const GruProblem& g, int ks) {
+  auto run_gru = [&](const GruProblem& g, const SplitW& sp, int ks) {
+    if (m->split) {  // one segment: the state rows
+      const ASeg& sg = g.A.seg[0];
+      const SpA a{(const float*)sg.p, sg.gather, sg.gmax, sg.ld, sg.K, B, kSplitState, 0.f};
+      const SplitW* w = &sp;
+      return launch_gru_sp(&a, &w, &g.ep, 1, m->cus, st);
+    }
     // (the test switch's forced streaming skips the K split, which the
     // streamed form never takes, so that small batches reach it)
     return ks > 1 && !gemm_stream_forced(g_gemm_form.load(std::memory_order_relaxed))
                ? launch_gemm_gru_split(&g, 1, H, m->bf16, ks, gpart, B, gru_split_tm(B, H, m->bf16, m->cus), st)
                   : launch_gemm_gru(&g, 1, H, m->bf16, m->cus, st);
   };
-  if (e == hipSuccess) e = run_gru(g1, L.ks_g1);
+  if (e == hipSuccess) e = run_gru(g1, m->g1.sp, L.ks_g1);
   mark(NMT_PHASE_GRU1 + 1);
   // attention query q = s1 att_Wq
   QuerySrc qsrc{q, 1, 0};
@@ -905,7 +1037,8 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
     // a split query leaves its sums for the attention to add as it loads
     // them (the test switch's forced streaming writes q itself)
     ep.defer_reduce = L.ks_q > 1 && !gemm_stream_forced(g_gemm_form.load(std::memory_order_relaxed));
-    e = launch_gemm_plain(Tile::Small, make_a(B, {state_seg(s1, s1h, 0)}), m->att_Wq, ep, st, m->cus);
+    e = m->split ? launch_plain_sp(SpA{s1, nullptr, 0, H, H, B, kSplitState, 0.f}, m->att_Wq.sp, ep, m->cus, st)
+                 : launch_gemm_plain(Tile::Small, make_a(B, {state_seg(s1, s1h, 0)}), m->att_Wq, ep, st, m->cus);
     qsrc = ep.defer_reduce ? QuerySrc{ep.part, L.ks_q, (int64_t)B * Aw} : QuerySrc{q, 1, 0};
   }
   mark(NMT_PHASE_QUERY + 1);
@@ -942,7 +1075,7 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
       g2.ep.xin = c;
       g2.ep.ldx = m->cpw_ld;
     }
-    e = run_gru(g2, L.ks_g2);
+    e = run_gru(g2, m->g2.sp, L.ks_g2);
   }
   mark(NMT_PHASE_GRU2 + 1);
   // readout t = tanh(s_new Ws + x Wy + c Wc + b), with the model's tables
@@ -961,7 +1094,10 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
       ep.out16 = (__bf16*)t;
       ep.ldo = bf16_row(E);
     }
-    e = launch_gemm_plain(Tile::Small,
+    if (m->split)
+      e = launch_plain_sp(SpA{d_s_new, nullptr, 0, H, H, B, kSplitState, 0.f}, m->ro.sp, ep, m->cus, st);
+    else
+      e = launch_gemm_plain(Tile::Small,
                           m->precomp ? make_a(B, {make_seg(d_s_new, H, H, 0, m->kc)})
                                      : make_a(B, {make_seg(d_s_new, H, H, 0, m->kc), x_seg, c_seg}),
                           m->ro,
@@ -971,7 +1107,9 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
   // vocabulary projection with an online log-sum-exp per slice, then the combine
   // rows with one request: the vocabulary kernel also picks out its logit
   float* zreq = rq.req ? (float*)(ws + L.zreq) : nullptr;
-  if (e == hipSuccess)
+  if (e == hipSuccess && m->out.sp.d)
+    e = launch_vocab_sp(t, B, E, m->out.sp, V, part, L.nS, L.vtm, rq.req, rq.req_off, rq.nreq, zreq, st);
+  else if (e == hipSuccess)
     e = launch_vocab_lse(t, m->bf16, B, E, m->out, V, part, L.nS, L.vtm, rq.req, rq.req_off, rq.nreq, zreq, st);
   mark(NMT_PHASE_VOCAB + 1);
   if (e == hipSuccess)
@@ -1070,9 +1208,19 @@ static std::vector<void**> param_fields(nmt_model* m) {
   return f;
 }
 
+// (The parameters are a model's first allocations; what is derived from them
+// comes after and may differ, as the weights decide whether they are split.)
 static bool same_layout(const nmt_model* a, const nmt_model* b) {
+  auto params = [](const nmt_model* m) {
+    size_t n = 0;
+    while (n < m->mem.kind.size() && m->mem.kind[n] != kOther) ++n;
+    return n;
+  };
+  const size_t n = params(a);
   return memcmp(&a->dims, &b->dims, sizeof(nmt_dims)) == 0 && a->device == b->device && a->kc == b->kc &&
-         a->emb_ld == b->emb_ld && a->mem.bytes == b->mem.bytes && a->mem.kind == b->mem.kind;
+         a->emb_ld == b->emb_ld && a->precomp == b->precomp && n == params(b) &&
+         std::equal(a->mem.bytes.begin(), a->mem.bytes.begin() + n, b->mem.bytes.begin()) &&
+         std::equal(a->mem.kind.begin(), a->mem.kind.begin() + n, b->mem.kind.begin());
 }
 
 nmt_status nmt_model_average(int32_t K, nmt_model* const* models, const float* h_coef, void* stream,
@@ -1138,7 +1286,8 @@ nmt_status nmt_model_average(int32_t K, nmt_model* const* models, const float* h
     }
     // the tables are products of the weights, not averaged: rebuilt from the averages
     a->tab_x = a->tab_y = nullptr;
-    if (a->precomp) e = word_tables(a, st);
+    e = split_weights(a, st);
+    if (e == hipSuccess && a->precomp) e = word_tables(a, st);
     if (e == hipSuccess) e = a->mem.alloc((void**)&a->err, sizeof(int));
   }
   if (e == hipSuccess) e = hipMemsetAsync(a->err, 0, sizeof(int), st);

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <vector>
 
 #include "device.hpp"
 
@@ -58,6 +59,16 @@ extern std::atomic<int64_t> g_gemm_streamed;  // launches of the weight-streamin
 constexpr int kVocabTN = 32;                    // packing granularity of the output weights
 constexpr int kVocabSpare = 32;                 // zero columns past the last block (group loads stay inside)
 
+// fp32 products on the fp16 matrix cores (split.hip): weights as two fp16
+// halves of the fp32 value times 2^scale, packed by the wave.
+struct SplitW {
+  void* d = nullptr;
+  float* bias = nullptr;  // output weights: the bias times 2^(scale + kSplitReadout), one per column
+  int64_t blocks = 0;     // 32-column blocks (GRU: r, z, candidate of 32 units each)
+  int K = 0, steps = 0;   // rows of the matrix, and 16-k steps they are padded to
+  int scale = 0;
+};
+
 // A weight matrix packed for one kernel family: [Kpad/KV][Npad][KV] of fp32
 // (KV = 4) or bf16 (KV = 8), 16 bytes per (vector row, column).
 struct Packed {
@@ -70,6 +81,7 @@ struct Packed {
   // hold the bias (fp32: one row; bf16: hi, mid, lo parts summing to it).
   int Krows = 0;
   int nbias = 0;
+  SplitW sp;  // fp32 models whose weights allow it: the copy that the fp16 matrix cores read
 };
 
 enum class Tile { Small, Large };
@@ -259,6 +271,47 @@ hipError_t launch_masked_copy(int S, int Tpad, int C, const float* src, const in
                               hipStream_t st);
 hipError_t launch_masked_mean(int S, int Tpad, int C, const float* ctx, const int32_t* len, float* mean,
                               hipStream_t st);
+
+// A operand of the fp32 products on the fp16 matrix cores (split.hip): fp32 rows, row m being row gather[m] of p (zeros outside
+// [0, gmax)) or row m; scaled by 2^scale before they are split.
+struct SpA {
+  const float* p;
+  const int32_t* gather;
+  int32_t gmax;
+  int64_t ld;
+  int32_t K, M;
+  int32_t scale;
+  float limit;  // magnitude from which a row is computed by the fp32 MFMA (set by the launchers)
+};
+constexpr int kSplitReadout = 14;  // activations' scale: tanh readouts (at most 1)
+constexpr int kSplitState = 12;    // states and annotations (at most 1 from the model; up to 16 stay on the halves)
+constexpr int kSpLongK = 256;      // K from which the tile GEMM splits K between wave groups
+constexpr int kSpShortChunk = 4, kSpLongChunk = 16;  // steps a shorter (longer) K is padded to multiples of
+constexpr int kNoSplit = 1 << 20;
+constexpr int kSplitMinH = 256;  // hidden units from which the products besides the vocabulary's are split
+// bits of the largest magnitude of each packed column of W's first K rows
+// (out [Npad]), or of each row of x [rows x E]
+hipError_t launch_magnitudes(const Packed& W, int K, uint32_t* out, hipStream_t st);
+hipError_t launch_row_magnitudes(const float* x, int64_t rows, int E, uint32_t* out, hipStream_t st);
+// The scale exponent for a matrix with these column (or row) magnitudes, or
+// kNoSplit where the halves would hold some column less precisely than fp32
+// (see split.hip) or a value is not finite.
+int split_scale(const std::vector<uint32_t>& mags);
+int split_steps(int K, bool vocab);
+int64_t split_bytes(int64_t blocks, int steps);
+hipError_t launch_split_pack(const Packed& W, int K, int steps, int64_t blocks, int gru_hb, int scale, void* out,
+                             hipStream_t st);
+hipError_t launch_scaled_bias(const Packed& W, int scale, int64_t n, float* out, hipStream_t st);
+// One or two GRU problems of the same weight shape with the cell fused, and
+// a plain product with PlainEpi's epilogue (no K split, no bf16 output).
+hipError_t launch_gru_sp(const SpA* A, const SplitW* const* W, const GruEpi* ep, int nprob, int cus, hipStream_t st);
+hipError_t launch_plain_sp(const SpA& A, const SplitW& W, const PlainEpi& ep, int cus, hipStream_t st);
+// The vocabulary projection (launch_vocab_lse's results): row tile and
+// slices for M rows, and whether E and the packed size fit the kernel.
+void split_vocab_shape(int M, int V, int cus, int* tm, int* nS);
+bool split_vocab_fits(int E, int64_t blocks);
+hipError_t launch_vocab_sp(const float* t, int M, int E, const SplitW& W, int V, float2* part, int nS, int tm,
+                           const int32_t* req1, const int32_t* req_off, int nreq, float* zreq, hipStream_t st);
 
 // Several models at once: buffer pointers and weights, passed by value.
 constexpr int kMaxModels = 32;
