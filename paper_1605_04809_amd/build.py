@@ -13,7 +13,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnmt.so")
-SOURCES = ("kernels.hip", "split.hip", "api.hip", "forest.hip")
+SOURCES = ("kernels.hip", "split.hip", "encode.hip", "api.hip", "forest.hip")
 HOST_SOURCES = ("forest_host.cpp",)   # plain C++, compiled by the host compiler
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

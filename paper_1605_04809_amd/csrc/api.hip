@@ -108,6 +108,11 @@ struct nmt_model {
   // as A operands of the tables and the encoder
   bool split = false;
   int emb_scale_src = 0, emb_scale_tgt = 0;
+  // the encoder's recurrent weights for its one-launch form (encode.hip;
+  // null where their range does not allow fp32 ones as halves)
+  void* scan_W = nullptr;
+  int scan_scale = 0;
+  bool coop = false;  // the device takes cooperative launches
   Packed g1x, roy, cpw;
   int cpw_ld = 0;  // columns of a projection row: 3H + E, padded to the large tile
   float *tab_x = nullptr, *tab_y = nullptr;
@@ -134,6 +139,7 @@ struct nmt_source {
   int32_t* kbig = nullptr;  // [S] 1 where a sentence has keys too large for their factors
   float* gru_part = nullptr;  // encoder: the recurrent GRU's split-K sums [2][enc_ks][S][4H]
   int enc_ks = 1;
+  void* words = nullptr;  // encoder: the one-launch recurrence's hand-over words
   int32_t* len = nullptr;
   std::vector<int32_t> h_len;
 };
@@ -335,8 +341,15 @@ hipError_t split_weights(nmt_model* m, hipStream_t st) {
   const Item out = {&m->out, d.E, 0};
   m->split = false;
   m->out.sp = SplitW{};
+  m->scan_W = nullptr;
   for (const Item& it : all) it.W->sp = SplitW{};
-  if (m->bf16) return hipSuccess;
+  auto pack_scan = [&](int scale) {
+    m->scan_scale = scale;
+    hipError_t r = m->mem.alloc(&m->scan_W, scan_weight_bytes(d.H, m->bf16));
+    if (r == hipSuccess) r = launch_scan_pack(m->enc_U, d.H, m->bf16, gru_hb(m->bf16), scale, m->scan_W, st);
+    return r;
+  };
+  if (m->bf16) return pack_scan(0);
   size_t n = std::max(std::max(d.V_src, d.V), (int)m->out.Npad);
   for (const Item& it : all) n = std::max(n, (size_t)it.W->Npad);
   uint32_t* dev = nullptr;
@@ -383,6 +396,14 @@ hipError_t split_weights(nmt_model* m, hipStream_t st) {
     }
   }
   if (!fits) m->out.sp = SplitW{};
+  // the recurrence: one scale for both directions
+  std::vector<uint32_t> mags;
+  for (int dir = 0; dir < 2 && e == hipSuccess; ++dir) {
+    e = launch_magnitudes(m->enc_U[dir], d.H, dev, st);
+    if (fetch((size_t)m->enc_U[dir].Npad)) mags.insert(mags.end(), host.begin(), host.end());
+  }
+  const int rec_scale = e == hipSuccess ? split_scale(mags) : kNoSplit;
+  if (rec_scale != kNoSplit && e == hipSuccess) e = pack_scan(rec_scale);
   fits = e == hipSuccess && m->precomp && d.H >= kSplitMinH;
   for (const Item& it : all) fits = fits && plan(it, false);
   for (int i = 0; i < 2 && fits && e == hipSuccess; ++i) {
@@ -545,8 +566,10 @@ nmt_status new_source(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* h_le
   if (e == hipSuccess) e = src->mem.alloc((void**)&src->kbig, S * sizeof(int32_t));
   if (e == hipSuccess && with_scratch) e = src->mem.alloc((void**)&src->scratch, rows * 6 * d.H * sizeof(float));
   if (e == hipSuccess && with_scratch) {
-    src->enc_ks = encoder_ksplit(m, S);
-    if (src->enc_ks > 1)
+    const size_t words = m->coop && m->scan_W ? scan_words_bytes(S, Tpad, d.H, m->bf16, m->cus) : 0;
+    if (words > 0) e = src->mem.alloc(&src->words, words);
+    src->enc_ks = words > 0 ? 1 : encoder_ksplit(m, S);
+    if (e == hipSuccess && src->enc_ks > 1)
       e = src->mem.alloc((void**)&src->gru_part, (size_t)2 * src->enc_ks * S * 4 * d.H * sizeof(float));
   }
   if (e == hipSuccess)
@@ -682,6 +705,8 @@ nmt_status nmt_model_create(const nmt_dims* dims, const nmt_weights* w, nmt_mode
     delete m;
     return fail(NMT_EDEVICE, "cannot read the compute-unit count of device %d", m->device);
   }
+  int coop = 0;
+  m->coop = hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, m->device) == hipSuccess && coop;
   const int E = d.E, H = d.H, A = d.A, C = 2 * d.H, V = d.V;
   hipError_t e = hipSuccess;
   auto step = [&](hipError_t r) {
@@ -825,7 +850,25 @@ nmt_status nmt_encode(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* d_sr
   // past a sentence's length are written as zeros, which is also the
   // backward direction's initial state there.
   const int64_t ldc = (int64_t)Tpad * C, ldx = (int64_t)Tpad * 6 * H;
-  for (int t = 0; t < Tpad && e == hipSuccess; ++t) {
+  bool chain = src->words == nullptr;
+  if (e == hipSuccess && !chain) {  // (a stream under capture keeps the chain of plain launches)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    chain = hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+  }
+  if (e == hipSuccess && !chain) {
+    GruEpi b{};
+    b.brz = m->enc_bias.brz;
+    b.bni = m->enc_bias.bni;
+    b.bns = m->enc_bias.bns;
+    e = launch_enc_scan(m->scan_W, Xp, src->ctx, src->len, src->words, m->err, b, S, Tpad, H, m->bf16, m->scan_scale,
+                        m->cus, st);
+    if (e != hipSuccess) {  // a launch that does not fit the device as it is now: the chain computes it all again
+      (void)hipGetLastError();
+      e = hipSuccess;
+      chain = true;
+    }
+  }
+  for (int t = 0; t < Tpad && e == hipSuccess && chain; ++t) {
     GruProblem p[2];
     for (int dir = 0; dir < 2; ++dir) {
       const int pos = dir == 0 ? t : Tpad - 1 - t;
@@ -1419,6 +1462,7 @@ nmt_status nmt_stream_status(nmt_model* m, void* stream) {
   e = hipMemcpy(&flag, m->err, sizeof(int), hipMemcpyDeviceToHost);
   if (e == hipSuccess && flag) e = hipMemset(m->err, 0, sizeof(int));
   if (e != hipSuccess) return hip_fail(e, "nmt_stream_status");
+  if (flag & 2) return fail(NMT_EDEVICE, "the encoder's blocks did not run together in a call since the last status check");
   if (flag) return fail(NMT_ERANGE, "an id was out of range in a call since the last status check");
   return ok();
 }

@@ -313,6 +313,16 @@ bool split_vocab_fits(int E, int64_t blocks);
 hipError_t launch_vocab_sp(const float* t, int M, int E, const SplitW& W, int V, float2* part, int nS, int tm,
                            const int32_t* req1, const int32_t* req_off, int nreq, float* zreq, hipStream_t st);
 
+// The encoder's recurrence as one cooperative launch (encode.hip): the
+// recurrent weights of both directions in its packing (hb: units per packed
+// GRU tile; scale: fp32 models' exponent, split_scale), the scratch words of
+// a source (0: the launch does not take it), and the launch itself.
+size_t scan_weight_bytes(int H, bool bf16);
+hipError_t launch_scan_pack(const Packed (&U)[2], int H, bool bf16, int hb, int scale, void* out, hipStream_t st);
+size_t scan_words_bytes(int S, int Tpad, int H, bool bf16, int cus);
+hipError_t launch_enc_scan(const void* W, const float* xp, float* ctx, const int32_t* len, void* words, int* err,
+                           const GruEpi& bias, int S, int Tpad, int H, bool bf16, int scale, int cus, hipStream_t st);
+
 // Several models at once: buffer pointers and weights, passed by value.
 constexpr int kMaxModels = 32;
 struct ModelTable {
