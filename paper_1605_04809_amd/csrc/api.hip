@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <unordered_map>
@@ -75,6 +76,91 @@ struct Allocs {
   }
 };
 
+// Idle device blocks of one model's sources.  A decoder sets up and destroys
+// a source per sentence, and allocating its arrays (68 MB for 20 sentences of
+// 50 words at the paper's sizes) took longer than the encoder's kernels: 0.7
+// of 1.0 ms.  A destroyed source, after the wait for the device that it makes
+// anyway, leaves its block here for the model's next one.  Bounded by
+// kPoolBytes; freed with the model, and whenever a device allocation of the
+// library would fail otherwise.
+constexpr size_t kPoolBytes = (size_t)1 << 30;
+
+struct BlockPool {
+  std::mutex mu;
+  int device = -1;
+  bool closed = false;  // the model is gone: blocks are freed as they come back
+  std::vector<std::pair<void*, size_t>> idle;  // oldest first
+  size_t idle_bytes = 0;
+
+  void* take(size_t need, size_t* got) {  // the smallest idle block that holds need without wasting half of itself
+    std::lock_guard<std::mutex> lock(mu);
+    size_t best = idle.size();
+    for (size_t i = 0; i < idle.size(); ++i)
+      if (idle[i].second >= need && idle[i].second <= 2 * need + ((size_t)1 << 20) &&
+          (best == idle.size() || idle[i].second < idle[best].second))
+        best = i;
+    if (best == idle.size()) return nullptr;
+    void* p = idle[best].first;
+    *got = idle[best].second;
+    idle_bytes -= idle[best].second;
+    idle.erase(idle.begin() + best);
+    return p;
+  }
+  // Keeps the block, dropping the oldest ones past the bound; what must be freed is left in out.
+  void put(void* p, size_t n, std::vector<void*>& out) {
+    std::lock_guard<std::mutex> lock(mu);
+    if (closed || n > kPoolBytes) {
+      out.push_back(p);
+      return;
+    }
+    idle.emplace_back(p, n);
+    idle_bytes += n;
+    while (idle_bytes > kPoolBytes) {
+      out.push_back(idle.front().first);
+      idle_bytes -= idle.front().second;
+      idle.erase(idle.begin());
+    }
+  }
+  void drain(bool close, std::vector<void*>& out) {
+    std::lock_guard<std::mutex> lock(mu);
+    closed = closed || close;
+    for (const auto& b : idle) out.push_back(b.first);
+    idle.clear();
+    idle_bytes = 0;
+  }
+};
+
+// Every open pool, so that an allocation that fails can take back what they hold.
+std::mutex g_pools_mu;
+std::vector<std::shared_ptr<BlockPool>> g_pools;
+
+std::shared_ptr<BlockPool> open_pool(int device) {
+  auto p = std::make_shared<BlockPool>();
+  p->device = device;
+  std::lock_guard<std::mutex> lock(g_pools_mu);
+  g_pools.push_back(p);
+  return p;
+}
+bool free_idle_blocks() {  // true if anything was freed
+  std::vector<void*> out;
+  {
+    std::lock_guard<std::mutex> lock(g_pools_mu);
+    for (const auto& p : g_pools) p->drain(false, out);
+  }
+  for (void* p : out) (void)hipFree(p);
+  return !out.empty();
+}
+void close_pool(const std::shared_ptr<BlockPool>& p) {
+  if (!p) return;
+  std::vector<void*> out;
+  {
+    std::lock_guard<std::mutex> lock(g_pools_mu);
+    g_pools.erase(std::remove(g_pools.begin(), g_pools.end(), p), g_pools.end());
+  }
+  p->drain(true, out);
+  for (void* q : out) (void)hipFree(q);
+}
+
 struct GruBias {
   float *brz = nullptr, *bni = nullptr, *bns = nullptr;
 };
@@ -113,6 +199,7 @@ struct nmt_model {
   void* scan_W = nullptr;
   int scan_scale = 0;
   bool coop = false;  // the device takes cooperative launches
+  std::shared_ptr<BlockPool> pool;  // its sources' idle blocks
   Packed g1x, roy, cpw;
   int cpw_ld = 0;  // columns of a projection row: 3H + E, padded to the large tile
   float *tab_x = nullptr, *tab_y = nullptr;
@@ -129,7 +216,9 @@ struct nmt_model {
 struct nmt_source {
   int32_t S = 0, Tpad = 0;
   int32_t H = 0, A = 0, cpw_ld = 0;  // the widths of the model that set it up
-  Allocs mem;
+  void* block = nullptr;  // every array below, from the model's pool
+  size_t block_bytes = 0;
+  std::shared_ptr<BlockPool> pool;
   float *ctx = nullptr, *pctx = nullptr, *scratch = nullptr;
   float* kfac = nullptr;  // 2^{2 log2(e) pctx}: the keys' factors of the attention scores
   // precomp models: per position, the annotation times the second GRU's
@@ -541,6 +630,40 @@ int encoder_ksplit(const nmt_model* m, int S) {
   return ks < 1 ? 1 : ks;
 }
 
+}  // namespace
+namespace nmt {
+static bool spend_budget();
+static hipError_t malloc_or_trim(void** p, size_t bytes);
+}  // namespace nmt
+namespace {
+
+// A block of at least `bytes` from the pool or the device; to the test hook
+// either is an allocation, alive until it is given back.
+hipError_t pooled_malloc(BlockPool& pool, void** p, size_t bytes, size_t* got) {
+  *p = nullptr;
+  if (!nmt::spend_budget()) return hipErrorOutOfMemory;
+  *p = pool.take(bytes, got);
+  if (*p) {
+    ++g_live_allocs;
+    return hipSuccess;
+  }
+  *got = bytes;
+  return nmt::malloc_or_trim(p, bytes);
+}
+// Back to the pool it came from, after the work that used it is done; a
+// caller on another device frees it there instead (it waited for the wrong one).
+void pooled_free(BlockPool& pool, void* p, size_t n) {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev != pool.device) {
+    device_free(p);
+    return;
+  }
+  --g_live_allocs;
+  std::vector<void*> out;
+  pool.put(p, n, out);
+  for (void* q : out) (void)hipFree(q);
+}
+
 nmt_status new_source(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* h_len, bool with_scratch,
                       hipStream_t st, nmt_source** out) {
   const nmt_dims& d = m->dims;
@@ -558,24 +681,42 @@ nmt_status new_source(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* h_le
   src->cpw_ld = m->precomp ? m->cpw_ld : 0;
   src->h_len.assign(h_len, h_len + S);
   const size_t rows = (size_t)S * Tpad;
-  hipError_t e = src->mem.alloc((void**)&src->ctx, rows * 2 * d.H * sizeof(float));
-  if (e == hipSuccess) e = src->mem.alloc((void**)&src->pctx, rows * d.A * sizeof(float));
-  if (e == hipSuccess) e = src->mem.alloc((void**)&src->kfac, rows * d.A * sizeof(float));
-  if (e == hipSuccess && m->precomp) e = src->mem.alloc((void**)&src->cproj, rows * m->cpw_ld * sizeof(float));
-  if (e == hipSuccess) e = src->mem.alloc((void**)&src->len, S * sizeof(int32_t));
-  if (e == hipSuccess) e = src->mem.alloc((void**)&src->kbig, S * sizeof(int32_t));
-  if (e == hipSuccess && with_scratch) e = src->mem.alloc((void**)&src->scratch, rows * 6 * d.H * sizeof(float));
-  if (e == hipSuccess && with_scratch) {
-    const size_t words = m->coop && m->scan_W ? scan_words_bytes(S, Tpad, d.H, m->bf16, m->cus) : 0;
-    if (words > 0) e = src->mem.alloc(&src->words, words);
+  size_t off = 0;
+  auto part = [&](size_t bytes) {
+    const size_t o = off;
+    off += (bytes + 255) / 256 * 256;
+    return o;
+  };
+  const size_t o_ctx = part(rows * 2 * d.H * sizeof(float)), o_pctx = part(rows * d.A * sizeof(float)),
+               o_kfac = part(rows * d.A * sizeof(float)),
+               o_cproj = part(m->precomp ? rows * m->cpw_ld * sizeof(float) : 0), o_len = part(S * sizeof(int32_t)),
+               o_kbig = part(S * sizeof(int32_t));
+  size_t o_scratch = 0, o_words = 0, o_part = 0, words = 0;
+  if (with_scratch) {
+    words = m->coop && m->scan_W ? scan_words_bytes(S, Tpad, d.H, m->bf16, m->cus) : 0;
     src->enc_ks = words > 0 ? 1 : encoder_ksplit(m, S);
-    if (e == hipSuccess && src->enc_ks > 1)
-      e = src->mem.alloc((void**)&src->gru_part, (size_t)2 * src->enc_ks * S * 4 * d.H * sizeof(float));
+    o_scratch = part(rows * 6 * d.H * sizeof(float));
+    o_words = part(words);
+    o_part = part(src->enc_ks > 1 ? (size_t)2 * src->enc_ks * S * 4 * d.H * sizeof(float) : 0);
+  }
+  src->pool = m->pool;
+  hipError_t e = pooled_malloc(*m->pool, &src->block, off, &src->block_bytes);
+  if (e == hipSuccess) {
+    char* base = (char*)src->block;
+    src->ctx = (float*)(base + o_ctx);
+    src->pctx = (float*)(base + o_pctx);
+    src->kfac = (float*)(base + o_kfac);
+    if (m->precomp) src->cproj = (float*)(base + o_cproj);
+    src->len = (int32_t*)(base + o_len);
+    src->kbig = (int32_t*)(base + o_kbig);
+    if (with_scratch) src->scratch = (float*)(base + o_scratch);
+    if (words > 0) src->words = base + o_words;
+    if (src->enc_ks > 1) src->gru_part = (float*)(base + o_part);
   }
   if (e == hipSuccess)
     e = hipMemcpyAsync(src->len, src->h_len.data(), S * sizeof(int32_t), hipMemcpyHostToDevice, st);
   if (e != hipSuccess) {
-    src->mem.release();
+    if (src->block) device_free(src->block);
     delete src;
     return hip_fail(e, "source allocation");
   }
@@ -632,18 +773,29 @@ hipError_t noalloc_scratch(int dev, void** out) {
 
 namespace nmt {
 
-hipError_t device_malloc(void** p, size_t bytes) {
+// One allocation of the test hook's budget; false where it is to fail.
+static bool spend_budget() {
   int64_t b = g_alloc_budget.load();
   while (b >= 0) {
-    if (b == 0) {
-      *p = nullptr;
-      return hipErrorOutOfMemory;
-    }
+    if (b == 0) return false;
     if (g_alloc_budget.compare_exchange_weak(b, b - 1)) break;
   }
-  const hipError_t e = hipMalloc(p, bytes);
+  return true;
+}
+
+static hipError_t malloc_or_trim(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory && free_idle_blocks()) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, bytes);
+  }
   if (e == hipSuccess) ++g_live_allocs;
   return e;
+}
+
+hipError_t device_malloc(void** p, size_t bytes) {
+  *p = nullptr;
+  return spend_budget() ? malloc_or_trim(p, bytes) : hipErrorOutOfMemory;
 }
 
 void device_free(void* p) {
@@ -801,6 +953,7 @@ nmt_status nmt_model_create(const nmt_dims* dims, const nmt_weights* w, nmt_mode
     delete m;
     return hip_fail(e, "nmt_model_create");
   }
+  m->pool = open_pool(m->device);
   *out = m;
   return ok();
 }
@@ -816,6 +969,7 @@ void nmt_model_destroy(nmt_model* m) {
   if (!m) return;
   (void)hipDeviceSynchronize();
   drop_profile_events(m);
+  close_pool(m->pool);
   m->mem.release();
   delete m;
 }
@@ -952,8 +1106,13 @@ nmt_status nmt_source_info(const nmt_source* src, int32_t* S, int32_t* Tpad, con
 
 void nmt_source_destroy(nmt_source* src) {
   if (!src) return;
-  (void)hipDeviceSynchronize();
-  src->mem.release();
+  const hipError_t e = hipDeviceSynchronize();
+  if (src->block) {
+    if (e == hipSuccess)
+      pooled_free(*src->pool, src->block, src->block_bytes);
+    else
+      device_free(src->block);
+  }
   delete src;
 }
 
@@ -1290,6 +1449,7 @@ nmt_status nmt_model_average(int32_t K, nmt_model* const* models, const float* h
   // Same dimensions and packing as models[0], fresh parameter buffers.
   nmt_model* a = new nmt_model(*m0);
   a->mem = Allocs{};
+  a->pool = nullptr;
   a->prof_events.clear();
   a->prof_on = false;
   a->prof_max = a->prof_used = 0;
@@ -1341,6 +1501,7 @@ nmt_status nmt_model_average(int32_t K, nmt_model* const* models, const float* h
     delete a;
     return hip_fail(e, "nmt_model_average");
   }
+  a->pool = open_pool(a->device);
   *out = a;
   return ok();
 }

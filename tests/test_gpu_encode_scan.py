@@ -72,3 +72,28 @@ def test_sources_on_two_streams_at_once():
         s.close()
     assert nb.nmt_stream_status(g.model) == nb.NMT_OK
     g.close()
+
+
+def test_source_blocks_come_back_and_outlive_their_model():
+    """A source set up in another source's old block (larger, smaller, equal)
+    is the one a fresh block gives; a source may be destroyed after its model."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_cases
+    from paper_1605_04809_amd import binding as nb
+    live = nb.debug_alloc_hook(-1)
+    wl = unit_gain(BASE.replace(S=9, H=100))
+    g = gpu_cases.GpuRun(wl)
+    ids = gpu_cases.cuda(wl.src_ids)
+    first = {}
+    for n in (9, 4, 9, 1, 5, 4, 9):
+        src = nb.nmt_encode(g.model, ids[:n].contiguous(), wl.src_len[:n])
+        ctx, pctx = (x.cpu().numpy() for x in src.copy_out())
+        want = first.setdefault(n, (ctx, pctx))
+        np.testing.assert_array_equal(ctx, want[0])
+        np.testing.assert_array_equal(pctx, want[1])
+        src.close()
+    g.model.close()
+    g.src.close()
+    assert nb.debug_alloc_hook(-1) == live
