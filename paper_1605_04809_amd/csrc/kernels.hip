@@ -1747,14 +1747,20 @@ __device__ __forceinline__ void store_c4(float* c, int64_t i, const f32x4& v, in
 __global__ __launch_bounds__(1024) void k_key_factors(int64_t per_sentence4, const f32x4* __restrict__ x,
                                                       f32x4* __restrict__ out, int32_t* __restrict__ big) {
   const int64_t base = (int64_t)blockIdx.x * per_sentence4;
+  // (an LDS flag: __syncthreads_or reads the block size from the dispatch
+  // packet, in host memory, about 5 us)
+  __shared__ int any;
+  if (threadIdx.x == 0) any = 0;
+  __syncthreads();
   bool b = false;
   for (int64_t i = threadIdx.x; i < per_sentence4; i += 1024) {
     const f32x4 v = x[base + i];
     b |= factor_big(v);
     out[base + i] = tanh_factor(v);
   }
-  b = __syncthreads_or(b);
-  if (threadIdx.x == 0) big[blockIdx.x] = b ? 1 : 0;
+  if (b) any = 1;
+  __syncthreads();
+  if (threadIdx.x == 0) big[blockIdx.x] = any;
 }
 
 hipError_t launch_key_factors(int S, int Tpad, int A, const float* pctx, float* kfac, int32_t* big, hipStream_t st) {
@@ -2104,10 +2110,12 @@ __device__ __forceinline__ void attention_tile(const int4 tl, int A, int C, int 
                                                const int32_t* __restrict__ kbig, const float* __restrict__ ctx,
                                                const int32_t* __restrict__ len, const int32_t* __restrict__ perm,
                                                const float* __restrict__ v, float* __restrict__ c,
-                                               float* __restrict__ alpha, f32x4* qs, float* e, int* rows, int wave,
+                                               float* __restrict__ alpha, f32x4* qs, float* e, int* rows,
+                                               int* any_big, int wave,
                                                int lane, int A4, int C4, int c_bf16, int npg) {
   constexpr int NT = NW * 64;
   const int s = tl.x, n = tl.z;
+  if (threadIdx.x == 0) *any_big = 0;
   if (threadIdx.x < G) rows[threadIdx.x] = (int)threadIdx.x < n ? (perm ? perm[tl.y + threadIdx.x] : tl.y + (int)threadIdx.x) : 0;
   __syncthreads();
   if (s < 0) {  // rows with an invalid sentence: flagged and NaN-ed by the combine kernel
@@ -2133,8 +2141,12 @@ __device__ __forceinline__ void attention_tile(const int4 tl, int A, int C, int 
     const int a4 = lane + 64 * k;
     vv[k] = a4 < A4 ? *(const f32x4*)(v + 4 * a4) * -2.f : zero4();
   }
-  const bool exact = __syncthreads_or(big) && kbig[s];
-  const int L = len[s];
+  // (an LDS flag and a plain barrier: __syncthreads_or reads the block size
+  // from the dispatch packet, in host memory, a wait of several us)
+  const int kb = kbig[s], L = len[s];
+  if (big) *any_big = 1;
+  __syncthreads();
+  const bool exact = *any_big && kb;
   // Tiles of fewer than 4 rows come from batches that leave the CUs short of
   // tiles, where a tile's latency sets the kernel's: a wave then loads the
   // keys of U positions (16 vectors a lane) before scoring any of them.
@@ -2275,7 +2287,7 @@ k_attention_grouped(
     float* __restrict__ alpha, int c_bf16, int round, int npg, int one_s, int one_sentence_B) {
   // queries [G][A/4] (later the context's partial sums [npg-1][G][C/4]), then scores [G][Tpad]
   extern __shared__ f32x4 dyn[];
-  __shared__ int rows[G];
+  __shared__ int rows[G], any_big;
   // one_sentence_B > 0: a batch of that many rows, all of sentence one_s,
   // tiled in row order with no grouping kernel (every tile the same length)
   const int nt = one_sentence_B > 0 ? (one_sentence_B + G - 1) / G : *n_tiles;
@@ -2295,7 +2307,7 @@ k_attention_grouped(
   }
   const int4 tl = one_sentence_B > 0 ? make_int4(one_s, t * G, min(G, one_sentence_B - t * G), 0) : tiles[t];
   attention_tile<G, NQ, NW>(tl, A, C, Tpad, q, kfac, pctx, kbig, ctx, len, one_sentence_B > 0 ? nullptr : perm, v, c,
-                            alpha, qs, e, rows, wave, lane, A4, C4, c_bf16, npg);
+                            alpha, qs, e, rows, &any_big, wave, lane, A4, C4, c_bf16, npg);
 }
 
 template <int G, int NQ>

@@ -252,7 +252,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   constexpr bool GRU = CF == 3;
   static_assert(NA >= 1 && TM * VPC % NT == 0 && NKL % VPF == 0, "whole vectors, ring slots fixed within a chunk");
   __shared__ f32x4 As[2 * 2 * VPC * TM];  // [stage][vector][hi, lo][row ^ vector]
-  __shared__ int wide[TM];
+  __shared__ int wide[TM], any_wide;
   constexpr int STG = 2 * VPC * TM;
   const SpProblem& Pb = batch.p[blockIdx.y];
   const SpA A = Pb.A;
@@ -366,8 +366,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
     for (int f = 0; f < CF; ++f) acc[i][f] = f32x16{};
   for (int i = threadIdx.x; i < TM; i += NT) wide[i] = 0;
+  if (threadIdx.x == 0) any_wide = 0;
 
-  if (nch > 0) {
+  if (nch > 0) {  // (without a product the flags below are never set)
     f32x4 ring[VPF][CF][2];
 #pragma unroll
     for (int p = 0; p < VPF; ++p) wload(ring[p], p / NKL, p % NKL);
@@ -426,7 +427,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   const bool busy = KS == 1 || kg * NPK < NP;
   auto piece_i = [&](int t) { return KS == 1 ? t / 4 : (kg * NPK + t) / 4 % RF; };
   auto piece_q = [&](int t) { return KS == 1 ? t % 4 : (kg * NPK + t) % 4; };
-  auto pick = [&](const int (&x)[RF], int i) { return RF == 1 || i == 0 ? x[0] : x[RF - 1]; };
+  // (by value: an array picked from at run time becomes LDS storage, addressed
+  // through the dispatch packet in host memory)
+  const int row_0 = row_i[0], row_1 = row_i[RF - 1], e0_0 = ext0[0], e0_1 = ext0[RF - 1], e1_0 = ext1[0],
+            e1_1 = ext1[RF - 1];
+  auto pick = [](int x0, int x1, int i) { return RF == 1 || i == 0 ? x0 : x1; };
   CellOps cop[GRU ? NB : 1];
   PlainOps pop[GRU ? 1 : NB][GRU ? 1 : CF];
   auto load_ops = [&](int t0) {
@@ -435,7 +440,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
       const int i = piece_i(t0 + b), q = piece_q(t0 + b);
       if constexpr (GRU) {
         const int H = Pb.g.H, j = cb0 / 3 * 32 + 8 * q + 4 * h;
-        const int hr = pick(ext0, i), xq = pick(ext1, i);
+        const int hr = pick(e0_0, e0_1, i), xq = pick(e1_0, e1_1, i);
         CellOps& o = cop[b];
         o.hp = o.xr = o.xz = o.xn = zero4();
         if (Pb.g.h) o.hp = load4_or0(Pb.g.h, (int64_t)hr * Pb.g.ldh + j, hr >= 0 && j < H);
@@ -447,7 +452,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
           o.xn = load4_or0(Pb.g.xin, x + 2 * H, ok);
         }
       } else {
-        const int ar = pick(ext0, i), row = pick(row_i, i);
+        const int ar = pick(e0_0, e0_1, i), row = pick(row_0, row_1, i);
 #pragma unroll
         for (int f = 0; f < CF; ++f) {
           const int n = (cb0 + f) * 32 + 8 * q + 4 * h;
@@ -493,14 +498,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
         sum[t][f] = f32x4{acc[i][f][4 * q], acc[i][f][4 * q + 1], acc[i][f][4 * q + 2], acc[i][f][4 * q + 3]};
       }
   }
-  bool big = false;
+  // (an LDS flag and a plain barrier: __syncthreads_or reads the block size
+  // from the dispatch packet, in host memory, which cost each launch 10 us)
 #pragma unroll
   for (int i = 0; i < NA; ++i)
     if (amax[i] >= A.limit) {
-      big = true;
       wide[arow + RP * i] = 1;
+      any_wide = 1;
     }
-  const bool any_wide = __syncthreads_or(big);
+  __syncthreads();
   if (!busy) return;
 #pragma unroll
   for (int t = 0; t < NPK; ++t)
@@ -542,7 +548,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     if constexpr (KS == 1) load_ops(t0);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      const int t = t0 + b, i = piece_i(t), q = piece_q(t), row = pick(row_i, i);
+      const int t = t0 + b, i = piece_i(t), q = piece_q(t), row = pick(row_0, row_1, i);
       if constexpr (GRU) {
         const GruEpi& ep = Pb.g;
         const int jl = 32 * wn + 8 * q + 4 * h, j = cb0 / 3 * 32 + 8 * q + 4 * h;
