@@ -51,6 +51,12 @@ int64_t nmt_debug_gemm_streamed(void);
  * other than 0 or 1. */
 int32_t nmt_debug_precompute(int32_t on);
 
+/* Whether small fp32 models run the step up to the readout as one kernel
+ * (1, the default) or as the separate kernels (0), so a test can compare the
+ * two, which give the same values.  Process-wide.  Returns the previous
+ * setting, or -1 (and changes nothing) for a value other than 0 or 1. */
+int32_t nmt_debug_small_step(int32_t on);
+
 #ifdef __cplusplus
 }
 #endif

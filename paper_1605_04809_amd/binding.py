@@ -38,7 +38,8 @@ EXPORTS = ("nmt_model_create", "nmt_model_destroy", "nmt_encode", "nmt_source_fr
            "nmt_forest_level", "nmt_forest_pair_paths", "nmt_forest_workspace_bytes", "nmt_score_forest",
            "nmt_forest_destroy", "nmt_model_average", "nmt_ensemble_workspace_bytes", "nmt_score_ensemble",
            "nmt_rescorer_create", "nmt_rescore_stack", "nmt_rescorer_info", "nmt_rescorer_destroy",
-           "nmt_debug_alloc_hook", "nmt_debug_gemm_form", "nmt_debug_gemm_streamed", "nmt_debug_precompute")
+           "nmt_debug_alloc_hook", "nmt_debug_gemm_form", "nmt_debug_gemm_streamed", "nmt_debug_precompute",
+           "nmt_debug_small_step")
 
 PHASES = ("gru1", "query", "attention", "gru2", "readout", "vocab", "combine")
 
@@ -121,6 +122,8 @@ def load_library(path: str = LIB_PATH):
     lib.nmt_debug_gemm_form.restype = _I32
     lib.nmt_debug_gemm_streamed.argtypes = []
     lib.nmt_debug_gemm_streamed.restype = ctypes.c_int64
+    lib.nmt_debug_small_step.argtypes = [_I32]
+    lib.nmt_debug_small_step.restype = _I32
     lib.nmt_debug_precompute.argtypes = [_I32]
     lib.nmt_debug_precompute.restype = _I32
     lib.nmt_last_error.argtypes = []
@@ -161,6 +164,13 @@ def debug_precompute(on: int) -> int:
     tables and projections (1, the default) or compute them per step (0);
     returns the previous setting."""
     return int(load_library().nmt_debug_precompute(on))
+
+
+def debug_small_step(on: int) -> int:
+    """Test hook (nmt_debug.h): whether small fp32 models run the step up to
+    the readout as one kernel (1, the default) or as the separate ones (0);
+    returns the previous setting."""
+    return int(load_library().nmt_debug_small_step(on))
 
 
 def last_error() -> str:

@@ -32,6 +32,7 @@ thread_local std::string g_err;
 std::atomic<int64_t> g_alloc_budget{-1};
 std::atomic<int64_t> g_live_allocs{0};
 std::atomic<int32_t> g_precompute{1};  // nmt_debug_precompute
+std::atomic<int32_t> g_small_step{1};  // nmt_debug_small_step
 
 nmt_status fail(nmt_status st, const char* fmt, ...) {
   char buf[512];
@@ -819,6 +820,11 @@ int32_t nmt_debug_gemm_form(int32_t form) {
 
 int64_t nmt_debug_gemm_streamed(void) { return nmt::g_gemm_streamed.load(); }
 
+int32_t nmt_debug_small_step(int32_t on) {
+  if (on != 0 && on != 1) return -1;
+  return g_small_step.exchange(on);
+}
+
 int32_t nmt_debug_precompute(int32_t on) {
   if (on != 0 && on != 1) return -1;
   return g_precompute.exchange(on);
@@ -1198,6 +1204,29 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
   };
   mark(0);
 
+  // small models: everything up to the readout in one kernel
+  const int small_R = m->precomp && !m->split && g_small_step.load(std::memory_order_relaxed)
+                          ? small_step_rows(B, H, Aw, E, src->Tpad, m->cus)
+                          : 0;
+  if (small_R > 0) {
+    const SmallStep p{pool, state_row, d_y_prev, d_sent_id, B, pool_rows, src->S, V, small_R, H, Aw, E, src->Tpad,
+                      m->cpw_ld, &m->g1, &m->att_Wq, &m->g2, &m->ro,
+                      {m->g1_bias.brz, m->g1_bias.bni, m->g1_bias.bns}, {m->g2_bias.brz, m->g2_bias.bni, m->g2_bias.bns},
+                      m->tab_x, m->tab_y, m->att_v, m->ro_b, src->kfac, src->pctx, src->cproj, src->kbig, src->len,
+                      s1, d_s_new, t, d_c ? q : nullptr, d_alpha};
+    if (e == hipSuccess) e = launch_step_small(p, st);
+    mark(NMT_PHASE_GRU1 + 1);
+    mark(NMT_PHASE_QUERY + 1);
+    if (e == hipSuccess && d_c) {
+      const AttnGroups grp =
+          pre_grp ? *pre_grp : AttnGroups{(int32_t*)(ws + L.perm), (int4*)(ws + L.tiles), (int32_t*)(ws + L.ntiles)};
+      e = launch_attention(B, Aw, C, src->Tpad, QuerySrc{q, 1, 0}, src->kfac, src->pctx, src->kbig, src->ctx, src->len,
+                           d_sent_id, src->S, m->att_v, d_c, nullptr, grp, false, m->cus, st, pre_grp != nullptr);
+    }
+    mark(NMT_PHASE_ATTENTION + 1);
+    mark(NMT_PHASE_GRU2 + 1);
+    mark(NMT_PHASE_READOUT + 1);
+  } else {
   // first GRU: s1 = GRU(x, s_prev), x = E_i the embeddings of the previous
   // words (ids outside the vocabulary, and -1, read zeros), or with the
   // model's tables their products with the input-side weights, rows y_prev
@@ -1306,6 +1335,7 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
                           ep, st, m->cus);
   }
   mark(NMT_PHASE_READOUT + 1);
+  }
   // vocabulary projection with an online log-sum-exp per slice, then the combine
   // rows with one request: the vocabulary kernel also picks out its logit
   float* zreq = rq.req ? (float*)(ws + L.zreq) : nullptr;

@@ -323,6 +323,25 @@ size_t scan_words_bytes(int S, int Tpad, int H, bool bf16, int cus);
 hipError_t launch_enc_scan(const void* W, const float* xp, float* ctx, const int32_t* len, void* words, int* err,
                            const GruEpi& bias, int S, int Tpad, int H, bool bf16, int scale, int cus, hipStream_t st);
 
+// The step up to the readout of a small fp32 model in one kernel
+// (k_step_small): rows per block for a batch of B rows (0: not taken), and
+// the launch.  q [B x A] and alpha [B x Tpad] are written if not NULL.
+struct SmallStep {
+  const float* pool;
+  const int32_t *state_row, *y_prev, *sent_id;
+  int32_t B, pool_rows, S, V, R, H, A, E, Tpad, cpw_ld;
+  const Packed *g1, *Wq, *g2, *ro;
+  struct Bias {
+    const float *brz, *bni, *bns;
+  } g1_bias, g2_bias;
+  const float *tab_x, *tab_y, *att_v, *ro_b;
+  const float *kfac, *pctx, *cproj;
+  const int32_t *kbig, *len;
+  float *s1, *s_new, *t, *q, *alpha;
+};
+int small_step_rows(int B, int H, int A, int E, int Tpad, int cus);
+hipError_t launch_step_small(const SmallStep& p, hipStream_t st);
+
 // Several models at once: buffer pointers and weights, passed by value.
 constexpr int kMaxModels = 32;
 struct ModelTable {

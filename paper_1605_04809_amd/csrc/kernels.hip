@@ -2445,6 +2445,329 @@ hipError_t launch_masked_copy(int S, int Tpad, int C, const float* src, const in
   return hipGetLastError();
 }
 
+// ------------------------------------------------ small models' step
+//
+// The step up to the readout for small fp32 models with the precomputed
+// products (H at most 128): first GRU, query, attention, second GRU and
+// readout of R rows in one block of 8 waves, activations in LDS, where the
+// separate kernels spend their time on launches and on each kernel's first
+// and last trips to memory (8 rows at H = 64: five kernels of 5 to 11 us for
+// 1 to 2 us of work each).  The products use the fp32 tile's MFMA in its
+// order of k (the weights as its row operand, which exchanges a product's
+// factors), the attention its order of terms and positions, so the results
+// are those of the separate kernels bit for bit.  R is the smallest power of
+// two that keeps the blocks to one per CU; past 8 rows a block's attention,
+// which reads a row's keys for that row alone, would outlast the grouped
+// kernel's.
+constexpr int kSmallH = 128, kSmallA = 256, kSmallE = 256, kSmallRows = 8;
+
+struct SmallArgs {
+  const float* pool;
+  const int32_t *state_row, *y_prev, *sent_id;
+  int32_t B, pool_rows, S, V, R, H, A, E, Tpad, cpw_ld, npg;
+  const f32x4 *g1, *Wq, *g2, *ro;
+  int64_t ng1, nWq, ng2, nro;  // packed columns
+  const float *tab_x, *tab_y, *brz1, *bni1, *bns1, *brz2, *bni2, *bns2, *v, *ro_b;
+  const float *kfac, *pctx, *cproj;
+  const int32_t *kbig, *len;
+  float *s1, *s_new, *t, *q, *alpha;  // q, alpha nullable (debug outputs)
+};
+
+// out(column, row l32, value) for every column of the tiles w, w + 8, ... of
+// a packed matrix, from rows X (LDS, stride ld, K columns, nrow of them).
+template <class Skip, class Out>
+__device__ __forceinline__ void small_gemm(const float* X, int ld, int K, int nrow, const f32x4* __restrict__ Wp,
+                                           int64_t Npad, int ntile, int wave, int lane, Skip&& skip, Out&& out) {
+  constexpr int U = 8;  // k groups of 8 in flight
+  const int h = lane >> 5, l32 = lane & 31, nkg = (K + 7) / 8;
+  const float* xr = X + (l32 < nrow ? l32 : 0) * ld;
+  for (int tile = wave; tile < ntile; tile += 8) {
+    if (skip(tile)) continue;
+    const f32x4* w = Wp + tile * 32 + l32;
+    auto load = [&](f32x4(&d)[U], int g0) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) d[u] = w[(int64_t)(2 * (g0 + u < nkg ? g0 + u : nkg - 1) + h) * Npad];
+    };
+    f32x16 acc = f32x16{};
+    f32x4 cur[U], nxt[U];
+    load(cur, 0);
+    for (int g0 = 0; g0 < nkg; g0 += U) {
+      load(nxt, g0 + U);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = 8 * (g0 + u) + 4 * h;
+        if (g0 + u >= nkg) break;
+        const f32x4 x = k < K ? *(const f32x4*)(xr + k) : zero4();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(cur[u][j], x[j], acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+    }
+    if (l32 < nrow)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) out(tile * 32 + acc_row(r, h), l32, acc[r]);
+  }
+}
+
+__global__ __launch_bounds__(512) void k_step_small(SmallArgs a) {
+  extern __shared__ float lds[];
+  const int H = a.H, A = a.A, E = a.E, R = a.R, HL = H + 4;
+  float* hs = lds;              // [R][HL] input state, later the new state
+  float* s1 = hs + R * HL;      // [R][HL]
+  float* pre = s1 + R * HL;     // [R][3H] gate sums
+  float* q = pre + R * 3 * H;   // [R][A] query
+  float* mix = q + R * A;       // [R][3H + E] the context's products
+  float* sc = mix + R * (3 * H + E);  // [R][Tpad] scores, then attention weights
+  __shared__ int y_s[kSmallRows], sr_s[kSmallRows], se_s[kSmallRows];
+  const int m0 = blockIdx.x * R, nrow = min(R, a.B - m0);
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  if (tid < R) {
+    const int row = m0 + (tid < nrow ? tid : 0);
+    const int y = a.y_prev[row], s = a.sent_id[row], r = a.state_row ? a.state_row[row] : row;
+    y_s[tid] = y >= 0 && y < a.V ? y : -1;
+    sr_s[tid] = r >= 0 && r < a.pool_rows ? r : -1;
+    // a source of one sentence takes every row as its own, as the grouped
+    // attention does; the combine flags the row
+    se_s[tid] = a.S == 1 ? 0 : (s >= 0 && s < a.S ? s : -1);
+  }
+  __syncthreads();
+  // the state rows, and the word's rows of the per-word tables (held until
+  // the cell and the readout need them)
+  for (int i = tid; i < R * (H / 4); i += 512) {
+    const int r = i / (H / 4), k = 4 * (i - r * (H / 4)), sr = sr_s[r];
+    *(f32x4*)(hs + r * HL + k) = sr >= 0 ? *(const f32x4*)(a.pool + (int64_t)sr * H + k) : zero4();
+  }
+  constexpr int NC = kSmallRows * kSmallH / 512, NE = kSmallRows * kSmallE / 512;  // cell and readout elements per thread
+  float xr[NC], xz[NC], xn[NC], ty[NE];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int i = tid + 512 * c, r = i / H, j = i - r * H;
+    const int y = r < R ? y_s[r] : -1;
+    const float* x = a.tab_x + (int64_t)(y >= 0 ? y : 0) * 3 * H + j;
+    xr[c] = y >= 0 ? x[0] : 0.f;
+    xz[c] = y >= 0 ? x[H] : 0.f;
+    xn[c] = y >= 0 ? x[2 * H] : 0.f;
+  }
+#pragma unroll
+  for (int c = 0; c < NE; ++c) {
+    const int i = tid + 512 * c, r = i / E, n = i - r * E;
+    const int y = r < R ? y_s[r] : -1;
+    ty[c] = y >= 0 ? a.tab_y[(int64_t)y * E + n] : 0.f;
+  }
+  __syncthreads();
+
+  // gate sums of state rows X: packed tiles of 32 columns, [r | z | n] of 64 units per six tiles
+  auto gates = [&](const float* X, const f32x4* W, int64_t Npad) {
+    small_gemm(
+        X, HL, H, nrow, W, Npad, (int)(Npad / 32), wave, lane,
+        [&](int tile) { return tile / 6 * 64 + tile % 2 * 32 >= H; },
+        [&](int col, int r, float v) {
+          const int u = col / (3 * kGruHB), rem = col - u * 3 * kGruHB, g = rem / kGruHB, j = u * kGruHB + rem % kGruHB;
+          if (j < H) pre[r * 3 * H + g * H + j] = v;
+        });
+  };
+  gates(hs, a.g1, a.ng1);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int i = tid + 512 * c, r = i / H, j = i - r * H;
+    if (r >= nrow) continue;
+    const float* p = pre + r * 3 * H + j;
+    const float s = gru_cell(p[0], p[H], 0.f, p[2 * H], a.brz1[j], a.brz1[H + j], a.bni1[j], a.bns1[j], xr[c], xz[c],
+                             xn[c], hs[r * HL + j]);
+    s1[r * HL + j] = s;
+    a.s1[(int64_t)(m0 + r) * H + j] = s;
+  }
+  __syncthreads();
+  small_gemm(
+      s1, HL, H, nrow, a.Wq, a.nWq, (A + 31) / 32, wave, lane, [](int) { return false; },
+      [&](int col, int r, float v) {
+        if (col < A) {
+          q[r * A + col] = v;
+          if (a.q) a.q[(int64_t)(m0 + r) * A + col] = v;
+        }
+      });
+  __syncthreads();
+
+  // attention: wave w's row
+  for (int r = wave; r < nrow; r += 8) {
+    const int s = se_s[r], A4 = A / 4;
+    float* e = sc + r * a.Tpad;
+    if (s < 0) {
+      for (int i = lane; i < a.Tpad; i += 64) e[i] = 0.f;
+    } else {
+      const int L = a.len[s];
+      const bool on = lane < A4;
+      const f32x4 qv = on ? *(const f32x4*)(q + r * A + 4 * lane) : zero4();
+      const f32x4 vv = on ? *(const f32x4*)(a.v + 4 * lane) * -2.f : zero4();
+      const bool exact = __builtin_amdgcn_ballot_w64(factor_big(qv)) != 0 && a.kbig[s];
+      const f32x4 qf = exact ? qv : tanh_factor(qv);
+      auto score = [&](auto exact_tag, const float* P) {
+        constexpr bool EX = decltype(exact_tag)::value;
+        constexpr int U = 8;  // positions in flight
+        for (int i0 = 0; i0 < L; i0 += U) {
+          f32x4 p[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            p[u] = on ? *(const f32x4*)(P + (int64_t)(i0 + u < L ? i0 + u : L - 1) * A + 4 * lane) : zero4();
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            float acc[1] = {0.f};
+            if (on)
+#pragma unroll
+              for (int x = 0; x < 4; ++x) acc[0] = score_term_t<EX>(p[u][x], qf[x], vv[x], acc[0]);
+            const float sum = wave_sums<1>(acc);
+            if (lane == 0 && i0 + u < L) e[i0 + u] = sum;
+          }
+        }
+      };
+      if (exact)
+        score(std::true_type{}, a.pctx + (int64_t)s * a.Tpad * A);
+      else
+        score(std::false_type{}, a.kfac + (int64_t)s * a.Tpad * A);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      float mx = -INFINITY;
+      for (int i = lane; i < L; i += 64) mx = fmaxf(mx, e[i]);
+      mx = wave_max(mx);
+      float sum = 0.f;
+      for (int i = lane; i < L; i += 64) sum += expf(e[i] - mx);
+      const float inv = 1.f / wave_sum(sum);
+      for (int i = lane; i < L; i += 64) e[i] = expf(e[i] - mx) * inv;
+    }
+    if (a.alpha) {
+      const int L = s < 0 ? 0 : a.len[s];
+      for (int i = lane; i < a.Tpad; i += 64) a.alpha[(int64_t)(m0 + r) * a.Tpad + i] = i < L ? e[i] : 0.f;
+    }
+  }
+  __syncthreads();
+  // the mix of the projections, in the grouped kernel's position groups
+  const int C4 = (3 * H + E) / 4;
+  for (int i = tid; i < nrow * C4; i += 512) {
+    const int r = i / C4, k4 = i - r * C4, s = se_s[r];
+    f32x4 total = zero4();
+    if (s >= 0) {
+      const int L = a.len[s];
+      const float* e = sc + r * a.Tpad;
+      const f32x4* X = (const f32x4*)(a.cproj + (int64_t)s * a.Tpad * a.cpw_ld) + k4;
+      const int64_t ldx = a.cpw_ld / 4;
+      for (int g = 0; g < a.npg; ++g) {
+        f32x4 acc = zero4();
+        constexpr int U = 8;
+        const int lo = L * g / a.npg, hi = L * (g + 1) / a.npg;
+        for (int p0 = lo; p0 < hi; p0 += U) {
+          f32x4 x[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) x[u] = X[(int64_t)(p0 + u < hi ? p0 + u : hi - 1) * ldx];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (p0 + u >= hi) break;
+            const float w = e[p0 + u];
+            acc[0] += w * x[u][0];
+            acc[1] += w * x[u][1];
+            acc[2] += w * x[u][2];
+            acc[3] += w * x[u][3];
+          }
+        }
+        total = g == 0 ? acc : total + acc;
+      }
+    }
+    *(f32x4*)(mix + r * (3 * H + E) + 4 * k4) = total;
+  }
+  gates(s1, a.g2, a.ng2);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int i = tid + 512 * c, r = i / H, j = i - r * H;
+    if (r >= nrow) continue;
+    const float* p = pre + r * 3 * H + j;
+    const float* x = mix + r * (3 * H + E) + j;
+    const float s = gru_cell(p[0], p[H], 0.f, p[2 * H], a.brz2[j], a.brz2[H + j], a.bni2[j], a.bns2[j], x[0], x[H],
+                             x[2 * H], s1[r * HL + j]);
+    hs[r * HL + j] = s;
+    a.s_new[(int64_t)(m0 + r) * H + j] = s;
+  }
+  __syncthreads();
+  float* ro = pre;  // [R][E], E at most 3H or the kernel is not taken
+  small_gemm(
+      hs, HL, H, nrow, a.ro, a.nro, (E + 31) / 32, wave, lane, [](int) { return false; },
+      [&](int col, int r, float v) {
+        if (col < E) ro[r * E + col] = v;
+      });
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < NE; ++c) {
+    const int i = tid + 512 * c, r = i / E, n = i - r * E;
+    if (r >= nrow) continue;
+    const float add = ty[c] + mix[r * (3 * H + E) + 3 * H + n];
+    a.t[(int64_t)(m0 + r) * E + n] = tanhf_(ro[i] + add + a.ro_b[n]);
+  }
+}
+
+// Rows per block for a batch of B rows, or 0 where the kernel is not taken.
+int small_step_rows(int B, int H, int A, int E, int Tpad, int cus) {
+  if (B <= 0 || H > kSmallH || A > kSmallA || E > kSmallE || E > 3 * H) return 0;
+  int R = 1;
+  while (R < kSmallRows && ceil_div(B, R) > cus) R *= 2;
+  if (ceil_div(B, R) > cus) return 0;
+  const size_t lds = (size_t)R * (2 * (H + 4) + 3 * H + A + 3 * H + E + Tpad) * 4;
+  return lds <= 120 * 1024 ? R : 0;
+}
+
+hipError_t launch_step_small(const SmallStep& p, hipStream_t st) {
+  SmallArgs a{};
+  a.pool = p.pool;
+  a.state_row = p.state_row;
+  a.y_prev = p.y_prev;
+  a.sent_id = p.sent_id;
+  a.B = p.B;
+  a.pool_rows = p.pool_rows;
+  a.S = p.S;
+  a.V = p.V;
+  a.R = p.R;
+  a.H = p.H;
+  a.A = p.A;
+  a.E = p.E;
+  a.Tpad = p.Tpad;
+  a.cpw_ld = p.cpw_ld;
+  const int C4 = p.cpw_ld / 4, nt = 2 * kAttnWaves * 64;
+  a.npg = (C4 % 64 == 0 && nt >= 2 * C4) ? nt / C4 : 1;  // as attention_grouped's blocks of 16 waves
+  a.g1 = (const f32x4*)p.g1->d;
+  a.ng1 = p.g1->Npad;
+  a.Wq = (const f32x4*)p.Wq->d;
+  a.nWq = p.Wq->Npad;
+  a.g2 = (const f32x4*)p.g2->d;
+  a.ng2 = p.g2->Npad;
+  a.ro = (const f32x4*)p.ro->d;
+  a.nro = p.ro->Npad;
+  a.tab_x = p.tab_x;
+  a.tab_y = p.tab_y;
+  a.brz1 = p.g1_bias.brz;
+  a.bni1 = p.g1_bias.bni;
+  a.bns1 = p.g1_bias.bns;
+  a.brz2 = p.g2_bias.brz;
+  a.bni2 = p.g2_bias.bni;
+  a.bns2 = p.g2_bias.bns;
+  a.v = p.att_v;
+  a.ro_b = p.ro_b;
+  a.kfac = p.kfac;
+  a.pctx = p.pctx;
+  a.cproj = p.cproj;
+  a.kbig = p.kbig;
+  a.len = p.len;
+  a.s1 = p.s1;
+  a.s_new = p.s_new;
+  a.t = p.t;
+  a.q = p.q;
+  a.alpha = p.alpha;
+  if (p.R < 1 || p.R > kSmallRows || p.R != small_step_rows(p.B, p.H, p.A, p.E, p.Tpad, ceil_div(p.B, p.R)))
+    return hipErrorInvalidValue;
+  const size_t lds = (size_t)p.R * (2 * (p.H + 4) + 3 * p.H + p.A + 3 * p.H + p.E + p.Tpad) * 4;
+  hipLaunchKernelGGL(k_step_small, dim3(ceil_div(p.B, p.R)), dim3(512), lds, st, a);
+  return hipGetLastError();
+}
+
 // mean over the unmasked positions of each sentence: a block per sentence and
 // 64 columns, so that short batches spread over the CUs (20 sentences of 50
 // positions: 70 us as one block of 256 threads per sentence).
