@@ -2473,36 +2473,48 @@ struct SmallArgs {
   float *s1, *s_new, *t, *q, *alpha;  // q, alpha nullable (debug outputs)
 };
 
+constexpr int kSmallU = 8;  // k groups of 8 in flight
+
+// The first kSmallU k groups of this wave's first tile, loaded well before
+// the product that needs them.
+struct SmallAhead {
+  f32x4 w[kSmallU];
+};
+__device__ __forceinline__ void small_load(SmallAhead& d, const f32x4* __restrict__ Wp, int64_t Npad, int tile, int g0,
+                                           int nkg, int lane) {
+  const f32x4* w = Wp + tile * 32 + (lane & 31);
+#pragma unroll
+  for (int u = 0; u < kSmallU; ++u) d.w[u] = w[(int64_t)(2 * (g0 + u < nkg ? g0 + u : nkg - 1) + (lane >> 5)) * Npad];
+}
+
 // out(column, row l32, value) for every column of the tiles w, w + 8, ... of
 // a packed matrix, from rows X (LDS, stride ld, K columns, nrow of them).
-template <class Skip, class Out>
+// first: the first tile's first block.  The next block, of this tile or the
+// next, is loaded during each block's MFMAs.
+template <class Out>
 __device__ __forceinline__ void small_gemm(const float* X, int ld, int K, int nrow, const f32x4* __restrict__ Wp,
-                                           int64_t Npad, int ntile, int wave, int lane, Skip&& skip, Out&& out) {
-  constexpr int U = 8;  // k groups of 8 in flight
+                                           int64_t Npad, int ntile, int wave, int lane, const SmallAhead& first,
+                                           Out&& out) {
+  constexpr int U = kSmallU;
   const int h = lane >> 5, l32 = lane & 31, nkg = (K + 7) / 8;
   const float* xr = X + (l32 < nrow ? l32 : 0) * ld;
+  SmallAhead cur = first;
   for (int tile = wave; tile < ntile; tile += 8) {
-    if (skip(tile)) continue;
-    const f32x4* w = Wp + tile * 32 + l32;
-    auto load = [&](f32x4(&d)[U], int g0) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) d[u] = w[(int64_t)(2 * (g0 + u < nkg ? g0 + u : nkg - 1) + h) * Npad];
-    };
     f32x16 acc = f32x16{};
-    f32x4 cur[U], nxt[U];
-    load(cur, 0);
     for (int g0 = 0; g0 < nkg; g0 += U) {
-      load(nxt, g0 + U);
+      SmallAhead nxt;
+      const bool more = g0 + U < nkg;
+      const int nt = more || tile + 8 >= ntile ? tile : tile + 8;
+      small_load(nxt, Wp, Npad, nt, more ? g0 + U : 0, nkg, lane);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int k = 8 * (g0 + u) + 4 * h;
         if (g0 + u >= nkg) break;
         const f32x4 x = k < K ? *(const f32x4*)(xr + k) : zero4();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(cur[u][j], x[j], acc, 0, 0, 0);
+        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(cur.w[u][j], x[j], acc, 0, 0, 0);
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+      cur = nxt;
     }
     if (l32 < nrow)
 #pragma unroll
@@ -2519,17 +2531,57 @@ __global__ __launch_bounds__(512) void k_step_small(SmallArgs a) {
   float* q = pre + R * 3 * H;   // [R][A] query
   float* mix = q + R * A;       // [R][3H + E] the context's products
   float* sc = mix + R * (3 * H + E);  // [R][Tpad] scores, then attention weights
-  __shared__ int y_s[kSmallRows], sr_s[kSmallRows], se_s[kSmallRows];
+  __shared__ int y_s[kSmallRows], sr_s[kSmallRows], se_s[kSmallRows], len_s[kSmallRows], kb_s[kSmallRows];
   const int m0 = blockIdx.x * R, nrow = min(R, a.B - m0);
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  // What depends on no id is loaded first: each product's first weights and
+  // the biases, so that later phases wait for no round trip of their own.
+  // Gate tiles: 32 units x [r | z | n] at a time, those past H left out.
+  const int nkg = (H + 7) / 8, ngate = (H + 31) / 32 * 3, nq = (A + 31) / 32, nr = (E + 31) / 32;
+  auto gate_tile = [&](int t) {  // packed tile of gate t % 3 of units 32 (t / 3) ..
+    const int u = t / 3;
+    return u / 2 * 6 + t % 3 * 2 + u % 2;
+  };
+  SmallAhead w1, wq, w2, wr;
+  small_load(w1, a.g1, a.ng1, gate_tile(min(wave, ngate - 1)), 0, nkg, lane);
+  int y_r = -1, s_r = -1, st_r = -1;
   if (tid < R) {
     const int row = m0 + (tid < nrow ? tid : 0);
-    const int y = a.y_prev[row], s = a.sent_id[row], r = a.state_row ? a.state_row[row] : row;
-    y_s[tid] = y >= 0 && y < a.V ? y : -1;
-    sr_s[tid] = r >= 0 && r < a.pool_rows ? r : -1;
+    y_r = a.y_prev[row];
+    s_r = a.sent_id[row];
+    st_r = a.state_row ? a.state_row[row] : row;
+  }
+  small_load(wq, a.Wq, a.nWq, min(wave, nq - 1), 0, nkg, lane);
+  small_load(w2, a.g2, a.ng2, gate_tile(min(wave, ngate - 1)), 0, nkg, lane);
+  small_load(wr, a.ro, a.nro, min(wave, nr - 1), 0, nkg, lane);
+  constexpr int NC = kSmallRows * kSmallH / 512, NE = kSmallRows * kSmallE / 512;  // cell and readout elements per thread
+  int cr[NC], cj[NC];
+  float b1[NC][4], b2[NC][4], tb[NE];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int i = tid + 512 * c;
+    cr[c] = i / H;
+    const int j = cj[c] = i - cr[c] * H;
+    b1[c][0] = a.brz1[j];
+    b1[c][1] = a.brz1[H + j];
+    b1[c][2] = a.bni1[j];
+    b1[c][3] = a.bns1[j];
+    b2[c][0] = a.brz2[j];
+    b2[c][1] = a.brz2[H + j];
+    b2[c][2] = a.bni2[j];
+    b2[c][3] = a.bns2[j];
+  }
+  const int A4 = A / 4;
+  const f32x4 vv = lane < A4 ? *(const f32x4*)(a.v + 4 * lane) * -2.f : zero4();
+  if (tid < R) {
+    y_s[tid] = y_r >= 0 && y_r < a.V ? y_r : -1;
+    sr_s[tid] = st_r >= 0 && st_r < a.pool_rows ? st_r : -1;
     // a source of one sentence takes every row as its own, as the grouped
     // attention does; the combine flags the row
-    se_s[tid] = a.S == 1 ? 0 : (s >= 0 && s < a.S ? s : -1);
+    const int s = a.S == 1 ? 0 : (s_r >= 0 && s_r < a.S ? s_r : -1);
+    se_s[tid] = s;
+    len_s[tid] = s >= 0 ? a.len[s] : 0;
+    kb_s[tid] = s >= 0 ? a.kbig[s] : 0;
   }
   __syncthreads();
   // the state rows, and the word's rows of the per-word tables (held until
@@ -2538,13 +2590,11 @@ __global__ __launch_bounds__(512) void k_step_small(SmallArgs a) {
     const int r = i / (H / 4), k = 4 * (i - r * (H / 4)), sr = sr_s[r];
     *(f32x4*)(hs + r * HL + k) = sr >= 0 ? *(const f32x4*)(a.pool + (int64_t)sr * H + k) : zero4();
   }
-  constexpr int NC = kSmallRows * kSmallH / 512, NE = kSmallRows * kSmallE / 512;  // cell and readout elements per thread
   float xr[NC], xz[NC], xn[NC], ty[NE];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    const int i = tid + 512 * c, r = i / H, j = i - r * H;
-    const int y = r < R ? y_s[r] : -1;
-    const float* x = a.tab_x + (int64_t)(y >= 0 ? y : 0) * 3 * H + j;
+    const int y = cr[c] < R ? y_s[cr[c]] : -1;
+    const float* x = a.tab_x + (int64_t)(y >= 0 ? y : 0) * 3 * H + cj[c];
     xr[c] = y >= 0 ? x[0] : 0.f;
     xz[c] = y >= 0 ? x[H] : 0.f;
     xn[c] = y >= 0 ? x[2 * H] : 0.f;
@@ -2554,154 +2604,169 @@ __global__ __launch_bounds__(512) void k_step_small(SmallArgs a) {
     const int i = tid + 512 * c, r = i / E, n = i - r * E;
     const int y = r < R ? y_s[r] : -1;
     ty[c] = y >= 0 ? a.tab_y[(int64_t)y * E + n] : 0.f;
+    tb[c] = a.ro_b[n];
   }
   __syncthreads();
 
-  // gate sums of state rows X: packed tiles of 32 columns, [r | z | n] of 64 units per six tiles
-  auto gates = [&](const float* X, const f32x4* W, int64_t Npad) {
-    small_gemm(
-        X, HL, H, nrow, W, Npad, (int)(Npad / 32), wave, lane,
-        [&](int tile) { return tile / 6 * 64 + tile % 2 * 32 >= H; },
-        [&](int col, int r, float v) {
-          const int u = col / (3 * kGruHB), rem = col - u * 3 * kGruHB, g = rem / kGruHB, j = u * kGruHB + rem % kGruHB;
-          if (j < H) pre[r * 3 * H + g * H + j] = v;
-        });
+  // gate sums of state rows X (the packed tile's loads address it through gate_tile)
+  auto gates = [&](const float* X, const f32x4* W, int64_t Npad, const SmallAhead& first) {
+    constexpr int U = kSmallU;
+    const int h = lane >> 5, l32 = lane & 31;
+    const float* xrow = X + (l32 < nrow ? l32 : 0) * HL;
+    SmallAhead cur = first;
+    for (int t = wave; t < ngate; t += 8) {
+      f32x16 acc = f32x16{};
+      for (int g0 = 0; g0 < nkg; g0 += U) {
+        SmallAhead nxt;
+        const bool more = g0 + U < nkg;
+        const int nt = more || t + 8 >= ngate ? t : t + 8;
+        small_load(nxt, W, Npad, gate_tile(nt), more ? g0 + U : 0, nkg, lane);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k = 8 * (g0 + u) + 4 * h;
+          if (g0 + u >= nkg) break;
+          const f32x4 x = k < H ? *(const f32x4*)(xrow + k) : zero4();
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(cur.w[u][j], x[j], acc, 0, 0, 0);
+        }
+        cur = nxt;
+      }
+      const int j0 = t / 3 * 32, g = t % 3;
+      if (l32 < nrow)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int j = j0 + acc_row(r, h);
+          if (j < H) pre[l32 * 3 * H + g * H + j] = acc[r];
+        }
+    }
   };
-  gates(hs, a.g1, a.ng1);
+  gates(hs, a.g1, a.ng1, w1);
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    const int i = tid + 512 * c, r = i / H, j = i - r * H;
+    const int r = cr[c], j = cj[c];
     if (r >= nrow) continue;
     const float* p = pre + r * 3 * H + j;
-    const float s = gru_cell(p[0], p[H], 0.f, p[2 * H], a.brz1[j], a.brz1[H + j], a.bni1[j], a.bns1[j], xr[c], xz[c],
-                             xn[c], hs[r * HL + j]);
+    const float s = gru_cell(p[0], p[H], 0.f, p[2 * H], b1[c][0], b1[c][1], b1[c][2], b1[c][3], xr[c], xz[c], xn[c],
+                             hs[r * HL + j]);
     s1[r * HL + j] = s;
     a.s1[(int64_t)(m0 + r) * H + j] = s;
   }
   __syncthreads();
-  small_gemm(
-      s1, HL, H, nrow, a.Wq, a.nWq, (A + 31) / 32, wave, lane, [](int) { return false; },
-      [&](int col, int r, float v) {
-        if (col < A) {
-          q[r * A + col] = v;
-          if (a.q) a.q[(int64_t)(m0 + r) * A + col] = v;
-        }
-      });
+  small_gemm(s1, HL, H, nrow, a.Wq, a.nWq, nq, wave, lane, wq, [&](int col, int r, float v) {
+    if (col < A) {
+      q[r * A + col] = v;
+      if (a.q) a.q[(int64_t)(m0 + r) * A + col] = v;
+    }
+  });
   __syncthreads();
 
-  // attention: wave w's row
-  for (int r = wave; r < nrow; r += 8) {
-    const int s = se_s[r], A4 = A / 4;
-    float* e = sc + r * a.Tpad;
-    if (s < 0) {
-      for (int i = lane; i < a.Tpad; i += 64) e[i] = 0.f;
-    } else {
-      const int L = a.len[s];
-      const bool on = lane < A4;
-      const f32x4 qv = on ? *(const f32x4*)(q + r * A + 4 * lane) : zero4();
-      const f32x4 vv = on ? *(const f32x4*)(a.v + 4 * lane) * -2.f : zero4();
-      const bool exact = __builtin_amdgcn_ballot_w64(factor_big(qv)) != 0 && a.kbig[s];
-      const f32x4 qf = exact ? qv : tanh_factor(qv);
-      auto score = [&](auto exact_tag, const float* P) {
-        constexpr bool EX = decltype(exact_tag)::value;
-        constexpr int U = 8;  // positions in flight
-        for (int i0 = 0; i0 < L; i0 += U) {
-          f32x4 p[U];
+  // attention: the 8 / R waves of a row share its positions
+  const int wpr = 8 / R, ar = wave / wpr, sub = wave % wpr;
+  if (ar < nrow && se_s[ar] >= 0) {
+    const int s = se_s[ar], L = len_s[ar];
+    float* e = sc + ar * a.Tpad;
+    const bool on = lane < A4;
+    const f32x4 qv = on ? *(const f32x4*)(q + ar * A + 4 * lane) : zero4();
+    const bool exact = __builtin_amdgcn_ballot_w64(factor_big(qv)) != 0 && kb_s[ar];
+    const f32x4 qf = exact ? qv : tanh_factor(qv);
+    auto score = [&](auto exact_tag, const float* P) {
+      constexpr bool EX = decltype(exact_tag)::value;
+      constexpr int U = 8;  // positions in flight
+      for (int i0 = sub; i0 < L; i0 += U * wpr) {
+        f32x4 p[U];
 #pragma unroll
-          for (int u = 0; u < U; ++u)
-            p[u] = on ? *(const f32x4*)(P + (int64_t)(i0 + u < L ? i0 + u : L - 1) * A + 4 * lane) : zero4();
+        for (int u = 0; u < U; ++u)
+          p[u] = on ? *(const f32x4*)(P + (int64_t)(i0 + u * wpr < L ? i0 + u * wpr : L - 1) * A + 4 * lane) : zero4();
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            float acc[1] = {0.f};
-            if (on)
+        for (int u = 0; u < U; ++u) {
+          if (i0 + u * wpr >= L) break;  // uniform over the wave
+          float acc[1] = {0.f};
+          if (on)
 #pragma unroll
-              for (int x = 0; x < 4; ++x) acc[0] = score_term_t<EX>(p[u][x], qf[x], vv[x], acc[0]);
-            const float sum = wave_sums<1>(acc);
-            if (lane == 0 && i0 + u < L) e[i0 + u] = sum;
-          }
+            for (int x = 0; x < 4; ++x) acc[0] = score_term_t<EX>(p[u][x], qf[x], vv[x], acc[0]);
+          const float sum = wave_sums<1>(acc);
+          if (lane == 0) e[i0 + u * wpr] = sum;
         }
-      };
-      if (exact)
-        score(std::true_type{}, a.pctx + (int64_t)s * a.Tpad * A);
-      else
-        score(std::false_type{}, a.kfac + (int64_t)s * a.Tpad * A);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      float mx = -INFINITY;
-      for (int i = lane; i < L; i += 64) mx = fmaxf(mx, e[i]);
-      mx = wave_max(mx);
-      float sum = 0.f;
-      for (int i = lane; i < L; i += 64) sum += expf(e[i] - mx);
-      const float inv = 1.f / wave_sum(sum);
-      for (int i = lane; i < L; i += 64) e[i] = expf(e[i] - mx) * inv;
-    }
-    if (a.alpha) {
-      const int L = s < 0 ? 0 : a.len[s];
-      for (int i = lane; i < a.Tpad; i += 64) a.alpha[(int64_t)(m0 + r) * a.Tpad + i] = i < L ? e[i] : 0.f;
-    }
+      }
+    };
+    if (exact)
+      score(std::true_type{}, a.pctx + (int64_t)s * a.Tpad * A);
+    else
+      score(std::false_type{}, a.kfac + (int64_t)s * a.Tpad * A);
   }
   __syncthreads();
-  // the mix of the projections, in the grouped kernel's position groups
+  if (sub == 0 && ar < nrow) {
+    const int L = len_s[ar];  // 0 for a row without a sentence
+    float* e = sc + ar * a.Tpad;
+    float mx = -INFINITY;
+    for (int i = lane; i < L; i += 64) mx = fmaxf(mx, e[i]);
+    mx = wave_max(mx);
+    float sum = 0.f;
+    for (int i = lane; i < L; i += 64) sum += expf(e[i] - mx);
+    const float inv = 1.f / wave_sum(sum);
+    for (int i = lane; i < L; i += 64) e[i] = expf(e[i] - mx) * inv;
+    if (a.alpha)
+      for (int i = lane; i < a.Tpad; i += 64) a.alpha[(int64_t)(m0 + ar) * a.Tpad + i] = i < L ? e[i] : 0.f;
+  }
+  __syncthreads();
+  // the mix of the projections, its sums cut where the grouped kernel's
+  // position groups are (L g / npg)
   const int C4 = (3 * H + E) / 4;
   for (int i = tid; i < nrow * C4; i += 512) {
-    const int r = i / C4, k4 = i - r * C4, s = se_s[r];
-    f32x4 total = zero4();
-    if (s >= 0) {
-      const int L = a.len[s];
-      const float* e = sc + r * a.Tpad;
-      const f32x4* X = (const f32x4*)(a.cproj + (int64_t)s * a.Tpad * a.cpw_ld) + k4;
-      const int64_t ldx = a.cpw_ld / 4;
-      for (int g = 0; g < a.npg; ++g) {
-        f32x4 acc = zero4();
-        constexpr int U = 8;
-        const int lo = L * g / a.npg, hi = L * (g + 1) / a.npg;
-        for (int p0 = lo; p0 < hi; p0 += U) {
-          f32x4 x[U];
+    const int r = i / C4, k4 = i - r * C4, s = se_s[r], L = len_s[r];
+    f32x4 total = zero4(), acc = zero4();
+    const float* e = sc + r * a.Tpad;
+    const f32x4* X = (const f32x4*)(a.cproj + (int64_t)max(s, 0) * a.Tpad * a.cpw_ld) + k4;
+    const int64_t ldx = a.cpw_ld / 4;
+    int g = 1, cut = L / a.npg;  // the next cut: L g / npg
+    constexpr int U = 8;
+    for (int p0 = 0; p0 < L; p0 += U) {
+      f32x4 x[U];
 #pragma unroll
-          for (int u = 0; u < U; ++u) x[u] = X[(int64_t)(p0 + u < hi ? p0 + u : hi - 1) * ldx];
+      for (int u = 0; u < U; ++u) x[u] = X[(int64_t)(p0 + u < L ? p0 + u : L - 1) * ldx];
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            if (p0 + u >= hi) break;
-            const float w = e[p0 + u];
-            acc[0] += w * x[u][0];
-            acc[1] += w * x[u][1];
-            acc[2] += w * x[u][2];
-            acc[3] += w * x[u][3];
-          }
+      for (int u = 0; u < U; ++u) {
+        if (p0 + u >= L) break;
+        while (p0 + u >= cut && g < a.npg) {
+          total += acc;
+          acc = zero4();
+          cut = L * ++g / a.npg;
         }
-        total = g == 0 ? acc : total + acc;
+        const float w = e[p0 + u];
+        acc[0] += w * x[u][0];
+        acc[1] += w * x[u][1];
+        acc[2] += w * x[u][2];
+        acc[3] += w * x[u][3];
       }
     }
-    *(f32x4*)(mix + r * (3 * H + E) + 4 * k4) = total;
+    *(f32x4*)(mix + r * (3 * H + E) + 4 * k4) = total + acc;
   }
-  gates(s1, a.g2, a.ng2);
+  gates(s1, a.g2, a.ng2, w2);
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    const int i = tid + 512 * c, r = i / H, j = i - r * H;
+    const int r = cr[c], j = cj[c];
     if (r >= nrow) continue;
     const float* p = pre + r * 3 * H + j;
     const float* x = mix + r * (3 * H + E) + j;
-    const float s = gru_cell(p[0], p[H], 0.f, p[2 * H], a.brz2[j], a.brz2[H + j], a.bni2[j], a.bns2[j], x[0], x[H],
-                             x[2 * H], s1[r * HL + j]);
+    const float s = gru_cell(p[0], p[H], 0.f, p[2 * H], b2[c][0], b2[c][1], b2[c][2], b2[c][3], x[0], x[H], x[2 * H],
+                             s1[r * HL + j]);
     hs[r * HL + j] = s;
     a.s_new[(int64_t)(m0 + r) * H + j] = s;
   }
   __syncthreads();
   float* ro = pre;  // [R][E], E at most 3H or the kernel is not taken
-  small_gemm(
-      hs, HL, H, nrow, a.ro, a.nro, (E + 31) / 32, wave, lane, [](int) { return false; },
-      [&](int col, int r, float v) {
-        if (col < E) ro[r * E + col] = v;
-      });
+  small_gemm(hs, HL, H, nrow, a.ro, a.nro, nr, wave, lane, wr, [&](int col, int r, float v) {
+    if (col < E) ro[r * E + col] = v;
+  });
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < NE; ++c) {
     const int i = tid + 512 * c, r = i / E, n = i - r * E;
     if (r >= nrow) continue;
     const float add = ty[c] + mix[r * (3 * H + E) + 3 * H + n];
-    a.t[(int64_t)(m0 + r) * E + n] = tanhf_(ro[i] + add + a.ro_b[n]);
+    a.t[(int64_t)(m0 + r) * E + n] = tanhf_(ro[i] + add + tb[c]);
   }
 }
 
