@@ -627,22 +627,39 @@ hipError_t launch_gru_sp(const SpA* A, const SplitW* const* W, const GruEpi* ep,
   }
   if (M <= 0) return hipSuccess;
   const int blocks = (int)W[0]->blocks;
-  auto fills = [&](int tm, int wn) { return nprob * sp_blocks(M, blocks, tm, 3 * wn) >= cus; };
   if (W[0]->K < kSpLongK) {
     if (M > 64)
       run_gemm_sp<2, 3, 2, 4, 1, kSpShortChunk>(b, nprob, M, blocks, st);
     else
       run_gemm_sp<1, 3, 2, 4, 1, kSpShortChunk>(b, nprob, M, blocks, st);
-  } else if (fills(128, 4)) {
-    run_gemm_sp<2, 3, 2, 4, 1, 8>(b, nprob, M, blocks, st);
-  } else if (fills(128, 2)) {
-    run_gemm_sp<2, 3, 2, 2, 2, 8>(b, nprob, M, blocks, st);
-  } else if (fills(128, 1)) {
-    run_gemm_sp<2, 3, 2, 1, 4, 8>(b, nprob, M, blocks, st);
-  } else if (fills(64, 1)) {
-    run_gemm_sp<2, 3, 1, 1, 8, 16>(b, nprob, M, blocks, st);
   } else {
-    run_gemm_sp<1, 3, 1, 1, 8, 16>(b, nprob, M, blocks, st);
+    // The tile whose launch is shortest: rounds of one block per CU, each as
+    // long as one block (measured at K = 1,024, in units of the smallest
+    // tile's 14.5 us: 64 x 32 21 us, 128 x 32 33 us, 128 x 64 57 us; two
+    // rounds of the smallest tile, 257 to 512 rows, 26 us against 21).
+    const struct {
+      int tm, wn;
+      double cost;
+    } tiles[] = {{128, 4, 7.4}, {128, 2, 3.9}, {128, 1, 2.3}, {64, 1, 1.45}, {32, 1, 1.0}};
+    int best = 0;
+    double best_cost = 0;
+    for (int i = 0; i < 5; ++i) {
+      const double c = ceil_div(nprob * sp_blocks(M, blocks, tiles[i].tm, 3 * tiles[i].wn), cus) * tiles[i].cost;
+      if (i == 0 || c < best_cost) {
+        best = i;
+        best_cost = c;
+      }
+    }
+    if (best == 0)
+      run_gemm_sp<2, 3, 2, 4, 1, 8>(b, nprob, M, blocks, st);
+    else if (best == 1)
+      run_gemm_sp<2, 3, 2, 2, 2, 8>(b, nprob, M, blocks, st);
+    else if (best == 2)
+      run_gemm_sp<2, 3, 2, 1, 4, 8>(b, nprob, M, blocks, st);
+    else if (best == 3)
+      run_gemm_sp<2, 3, 1, 1, 8, 16>(b, nprob, M, blocks, st);
+    else
+      run_gemm_sp<1, 3, 1, 1, 8, 16>(b, nprob, M, blocks, st);
   }
   return hipGetLastError();
 }
