@@ -187,7 +187,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
             waiting = false;
             if (lane == 0) atomicOr(a.err, 2);
           }
-          __builtin_amdgcn_s_sleep(1);
+          // Half a microsecond between polls: the polls of 1,024 waves share
+          // the path of the stores they wait for (sleeps of 64, 512, 1,024 and
+          // 1,536 cycles: 30 positions of one sentence 244, 233, 228 and 221 us
+          // a source, 80 of 32 bf16 ones 513, 504, 496 and 504 us).
+          __builtin_amdgcn_s_sleep(16);
         }
 #pragma unroll
         for (int i = 0; i < kScanWaveK; ++i) {
