@@ -2112,7 +2112,7 @@ __device__ __forceinline__ void attention_tile(const int4 tl, int A, int C, int 
                                                const float* __restrict__ v, float* __restrict__ c,
                                                float* __restrict__ alpha, f32x4* qs, float* e, int* rows,
                                                int* any_big, int wave,
-                                               int lane, int A4, int C4, int c_bf16, int npg) {
+                                               int lane, int A4, int C4, int c_bf16, int npg, int k_lo, int W4) {
   constexpr int NT = NW * 64;
   const int s = tl.x, n = tl.z;
   if (threadIdx.x == 0) *any_big = 0;
@@ -2120,7 +2120,8 @@ __device__ __forceinline__ void attention_tile(const int4 tl, int A, int C, int 
   __syncthreads();
   if (s < 0) {  // rows with an invalid sentence: flagged and NaN-ed by the combine kernel
     for (int g = 0; g < n; ++g) {
-      for (int k4 = threadIdx.x; k4 < C4; k4 += NT) store_c4(c, (int64_t)rows[g] * C + 4 * k4, zero4(), c_bf16);
+      for (int k4 = threadIdx.x; k4 < W4; k4 += NT)
+        store_c4(c, (int64_t)rows[g] * C + 4 * (k_lo + k4), zero4(), c_bf16);
       if (alpha)
         for (int i = threadIdx.x; i < Tpad; i += NT) alpha[(int64_t)rows[g] * Tpad + i] = 0.f;
     }
@@ -2215,11 +2216,11 @@ __device__ __forceinline__ void attention_tile(const int4 tl, int A, int C, int 
   // contiguous ranges of positions, and group 0 adds the other groups'
   // partial sums (left in LDS over the queries, dead by now) in group order:
   // each thread then waits for a fraction of the annotations' round trips.
-  const f32x4* X = (const f32x4*)(ctx + (int64_t)s * Tpad * C);
-  const int pg = npg > 1 ? (int)threadIdx.x / C4 : 0;
+  const f32x4* X = (const f32x4*)(ctx + (int64_t)s * Tpad * C) + k_lo;  // this block's columns: W4 from k_lo on
+  const int pg = npg > 1 ? (int)threadIdx.x / W4 : 0;
   const int i_lo = npg > 1 ? L * pg / npg : 0, i_hi = npg > 1 ? L * (pg + 1) / npg : L;
-  const int k_first = npg > 1 ? (int)threadIdx.x - pg * C4 : (int)threadIdx.x;
-  for (int k4 = k_first; k4 < C4 && pg < npg; k4 += (npg > 1 ? C4 : NT)) {
+  const int k_first = npg > 1 ? (int)threadIdx.x - pg * W4 : (int)threadIdx.x;
+  for (int k4 = k_first; k4 < W4 && pg < npg; k4 += (npg > 1 ? W4 : NT)) {
     f32x4 acc[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) acc[g] = zero4();
@@ -2252,22 +2253,22 @@ __device__ __forceinline__ void attention_tile(const int4 tl, int A, int C, int 
     if (npg > 1) {
       if (pg > 0) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) qs[((pg - 1) * G + g) * C4 + k4] = acc[g];
+        for (int g = 0; g < G; ++g) qs[((pg - 1) * G + g) * W4 + k4] = acc[g];
       }
       __syncthreads();
       if (pg == 0) {
         for (int q = 1; q < npg; ++q)
 #pragma unroll
-          for (int g = 0; g < G; ++g) acc[g] += qs[((q - 1) * G + g) * C4 + k4];
+          for (int g = 0; g < G; ++g) acc[g] += qs[((q - 1) * G + g) * W4 + k4];
       }
     }
     if (pg == 0) {
 #pragma unroll
       for (int g = 0; g < G; ++g)
-        if (g < n) store_c4(c, (int64_t)rows[g] * C + 4 * k4, acc[g], c_bf16);
+        if (g < n) store_c4(c, (int64_t)rows[g] * C + 4 * (k_lo + k4), acc[g], c_bf16);
     }
   }
-  if (npg > 1 && (int)threadIdx.x >= npg * C4) __syncthreads();  // threads without a column still meet the barrier
+  if (npg > 1 && (int)threadIdx.x >= npg * W4) __syncthreads();  // threads without a column still meet the barrier
 }
 
 // One block (NW waves) per tile of up to G rows of one sentence.  The rows'
@@ -2284,7 +2285,7 @@ k_attention_grouped(
     const int32_t* __restrict__ kbig, const float* __restrict__ ctx, const int32_t* __restrict__ len,
     const int32_t* __restrict__ perm, const int4* __restrict__ tiles,
     const int32_t* __restrict__ n_tiles, const float* __restrict__ v, float* __restrict__ c,
-    float* __restrict__ alpha, int c_bf16, int round, int npg, int one_s, int one_sentence_B) {
+    float* __restrict__ alpha, int c_bf16, int round, int npg, int one_s, int one_sentence_B, int W4) {
   // queries [G][A/4] (later the context's partial sums [npg-1][G][C/4]), then scores [G][Tpad]
   extern __shared__ f32x4 dyn[];
   __shared__ int rows[G], any_big;
@@ -2292,9 +2293,12 @@ k_attention_grouped(
   // tiled in row order with no grouping kernel (every tile the same length)
   const int nt = one_sentence_B > 0 ? (one_sentence_B + G - 1) / G : *n_tiles;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // C4 / W4 blocks (blockIdx.y) share a tile's columns of the context, each
+  // with the tile's scores of its own
   const int A4 = A / 4, C4 = C / 4;
   f32x4* qs = dyn;
-  float* e = (float*)(dyn + max(G * A4, (npg - 1) * G * C4));
+  float* e = (float*)(dyn + max(G * A4, (npg - 1) * G * W4));
+  if (blockIdx.y > 0) alpha = nullptr;
   int t = blockIdx.x;
   if (t >= nt) return;
   // Blocks are handed to the CUs in order, one per CU per round of `round`
@@ -2307,7 +2311,8 @@ k_attention_grouped(
   }
   const int4 tl = one_sentence_B > 0 ? make_int4(one_s, t * G, min(G, one_sentence_B - t * G), 0) : tiles[t];
   attention_tile<G, NQ, NW>(tl, A, C, Tpad, q, kfac, pctx, kbig, ctx, len, one_sentence_B > 0 ? nullptr : perm, v, c,
-                            alpha, qs, e, rows, &any_big, wave, lane, A4, C4, c_bf16, npg);
+                            alpha, qs, e, rows, &any_big, wave, lane, A4, C4, c_bf16, npg,
+                            (int)blockIdx.y * W4, W4);
 }
 
 template <int G, int NQ>
@@ -2318,12 +2323,23 @@ static void attention_grouped(int B, int A, int C, int Tpad, QuerySrc q, const f
   const int grid = one_s >= 0 ? ceil_div(B, G) : (int)std::min<int64_t>(B, (int64_t)ceil_div(B, G) + S + 1);
   const int one_B = one_s >= 0 ? B : 0;
   const int round = NMT_ATTN_SNAKE ? cus : 0;
-  // Position groups of the context phase: whole waves per group (C/4 a
-  // multiple of 64), so every wave meets its one barrier.
   const int C4 = C / 4;
-  auto groups = [&](int nt) { return (C4 % 64 == 0 && nt >= 2 * C4) ? nt / C4 : 1; };
+  // A handful of tiles (a beam): more blocks per tile, each mixing a part of
+  // the columns, so that a thread's chain of annotation loads is shorter (12
+  // rows: step 78.3 -> 74.8 us).  Each part scores the positions anew: with
+  // 125 tiles and more that cost more than it gave (250 tiles in two parts:
+  // ruen step 256 -> 263 us).  Parts are whole waves of float4 columns.
+  int parts = 1;
+  const int64_t tiles = ceil_div(B, G);
+  if (C4 >= 512 && 8 * tiles <= cus)
+    for (int p : {2, 4, 7, 8, 14})
+      if (C4 % (64 * p) == 0 && p * tiles <= cus) parts = p;
+  const int W4 = C4 / parts;
+  // Position groups of the context phase: whole waves per group (W4 a
+  // multiple of 64), so every wave meets its one barrier.
+  auto groups = [&](int nt) { return (W4 % 64 == 0 && nt >= 2 * W4) ? nt / W4 : 1; };
   auto lds_bytes = [&](int npg) {
-    return (size_t)std::max(G * (A / 4), (npg - 1) * G * C4) * 16 + (size_t)G * Tpad * 4;
+    return (size_t)std::max(G * (A / 4), (npg - 1) * G * W4) * 16 + (size_t)G * Tpad * 4;
   };
   // Few tiles (about two per CU or fewer, e.g. 2,000 rows in 20 sentences)
   // leave the CUs short of waves to hide memory latency with: twice the
@@ -2332,14 +2348,14 @@ static void attention_grouped(int B, int A, int C, int Tpad, QuerySrc q, const f
   // faster (70.6 against 75.1 us).
   if (grid <= kAttnWideTiles) {
     const int npg = groups(2 * kAttnWaves * 64);
-    hipLaunchKernelGGL((k_attention_grouped<G, NQ, 2 * kAttnWaves>), dim3(grid), dim3(2 * kAttnWaves * 64),
+    hipLaunchKernelGGL((k_attention_grouped<G, NQ, 2 * kAttnWaves>), dim3(grid, parts), dim3(2 * kAttnWaves * 64),
                        lds_bytes(npg), st, A, C, Tpad, q, kfac, pctx, kbig, ctx, len, grp.perm, grp.tiles, grp.n_tiles,
-                       v, c, alpha, c_bf16, round, npg, one_s, one_B);
+                       v, c, alpha, c_bf16, round, npg, one_s, one_B, W4);
   } else {
     const int npg = groups(kAttnWaves * 64);
-    hipLaunchKernelGGL((k_attention_grouped<G, NQ, kAttnWaves>), dim3(grid), dim3(kAttnWaves * 64), lds_bytes(npg), st,
+    hipLaunchKernelGGL((k_attention_grouped<G, NQ, kAttnWaves>), dim3(grid, parts), dim3(kAttnWaves * 64), lds_bytes(npg), st,
                        A, C, Tpad, q, kfac, pctx, kbig, ctx, len, grp.perm, grp.tiles, grp.n_tiles, v, c, alpha, c_bf16,
-                       round, npg, one_s, one_B);
+                       round, npg, one_s, one_B, W4);
   }
 }
 
