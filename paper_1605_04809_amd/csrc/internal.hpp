@@ -288,7 +288,11 @@ constexpr int kSplitState = 12;    // states and annotations (at most 1 from the
 constexpr int kSpLongK = 256;      // K from which the tile GEMM splits K between wave groups
 constexpr int kSpShortChunk = 4, kSpLongChunk = 16;  // steps a shorter (longer) K is padded to multiples of
 constexpr int kNoSplit = 1 << 20;
-constexpr int kSplitMinH = 256;  // hidden units from which the products besides the vocabulary's are split
+// Hidden units from which the products besides the vocabulary's are split: a
+// smaller model's step is launches and round trips (the split tiles at H = 64:
+// 43.4 us a step against 44.4), and at H of at most 128 one kernel.
+constexpr int kSplitMinH = 256;
+static_assert(kSplitMinH >= kSpLongK, "the GRU tiles take a long K");
 // bits of the largest magnitude of each packed column of W's first K rows
 // (out [Npad]), or of each row of x [rows x E]
 hipError_t launch_magnitudes(const Packed& W, int K, uint32_t* out, hipStream_t st);

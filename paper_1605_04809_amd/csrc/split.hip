@@ -198,10 +198,18 @@ hipError_t launch_scaled_bias(const Packed& W, int scale, int64_t n, float* out,
 // operand, so a lane's accumulator registers are runs of four consecutive
 // columns (units) of one batch row and the epilogues load and store 16 bytes.
 //
-// Which tile: the largest that gives every CU a block, as a larger one reads
-// its operands from L2 less often; smaller ones trade that for more blocks,
-// and the k groups keep 8 waves on a CU whatever the tile.  Short K takes
-// one k group and short chunks, whose sums do not depend on the tile.
+// What bounds it: the operands' way from L2 (544 MB a launch for a GRU of
+// 2,000 rows) and the fixed ends of a block (first chunk, sums of the k
+// groups, the cell's operands).  A GRU of 2,000 rows, 1,024 units: 104.2 us
+// with fp32 MFMAs, 57 us here.
+//
+// Which tile: a larger one reads its operands from L2 less often, smaller
+// ones trade that for more blocks; the k groups keep 8 waves on a CU whatever
+// the tile.  The GRU takes the tile whose launch is shortest by rounds of
+// blocks times their measured length (launch_gru_sp), the plain products the
+// largest tile that gives every CU a block (launch_plain_sp).  K below
+// kSpLongK takes one k group and short chunks, whose sums do not depend on
+// the tile.
 //
 // Wide rows.  A row with an element at or beyond the halves' range (or an
 // infinity) is computed again by the fp32 MFMA from the fp32 row and the
@@ -627,40 +635,34 @@ hipError_t launch_gru_sp(const SpA* A, const SplitW* const* W, const GruEpi* ep,
   }
   if (M <= 0) return hipSuccess;
   const int blocks = (int)W[0]->blocks;
-  if (W[0]->K < kSpLongK) {
-    if (M > 64)
-      run_gemm_sp<2, 3, 2, 4, 1, kSpShortChunk>(b, nprob, M, blocks, st);
-    else
-      run_gemm_sp<1, 3, 2, 4, 1, kSpShortChunk>(b, nprob, M, blocks, st);
-  } else {
-    // The tile whose launch is shortest: rounds of one block per CU, each as
-    // long as one block (measured at K = 1,024, in units of the smallest
-    // tile's 14.5 us: 64 x 32 21 us, 128 x 32 33 us, 128 x 64 57 us; two
-    // rounds of the smallest tile, 257 to 512 rows, 26 us against 21).
-    const struct {
-      int tm, wn;
-      double cost;
-    } tiles[] = {{128, 4, 7.4}, {128, 2, 3.9}, {128, 1, 2.3}, {64, 1, 1.45}, {32, 1, 1.0}};
-    int best = 0;
-    double best_cost = 0;
-    for (int i = 0; i < 5; ++i) {
-      const double c = ceil_div(nprob * sp_blocks(M, blocks, tiles[i].tm, 3 * tiles[i].wn), cus) * tiles[i].cost;
-      if (i == 0 || c < best_cost) {
-        best = i;
-        best_cost = c;
-      }
+  if (W[0]->K < kSpLongK) return hipErrorInvalidValue;  // models of fewer units keep the fp32 MFMA (kSplitMinH)
+  // The tile whose launch is shortest: rounds of one block per CU, each as
+  // long as one block (measured at K = 1,024, in units of the smallest
+  // tile's 14.5 us: 64 x 32 21 us, 128 x 32 33 us, 128 x 64 57 us; two
+  // rounds of the smallest tile, 257 to 512 rows, 26 us against 21).
+  const struct {
+    int tm, wn;
+    double cost;
+  } tiles[] = {{128, 4, 7.4}, {128, 2, 3.9}, {128, 1, 2.3}, {64, 1, 1.45}, {32, 1, 1.0}};
+  int best = 0;
+  double best_cost = 0;
+  for (int i = 0; i < 5; ++i) {
+    const double c = ceil_div(nprob * sp_blocks(M, blocks, tiles[i].tm, 3 * tiles[i].wn), cus) * tiles[i].cost;
+    if (i == 0 || c < best_cost) {
+      best = i;
+      best_cost = c;
     }
-    if (best == 0)
-      run_gemm_sp<2, 3, 2, 4, 1, 8>(b, nprob, M, blocks, st);
-    else if (best == 1)
-      run_gemm_sp<2, 3, 2, 2, 2, 8>(b, nprob, M, blocks, st);
-    else if (best == 2)
-      run_gemm_sp<2, 3, 2, 1, 4, 8>(b, nprob, M, blocks, st);
-    else if (best == 3)
-      run_gemm_sp<2, 3, 1, 1, 8, 16>(b, nprob, M, blocks, st);
-    else
-      run_gemm_sp<1, 3, 1, 1, 8, 16>(b, nprob, M, blocks, st);
   }
+  if (best == 0)
+    run_gemm_sp<2, 3, 2, 4, 1, 8>(b, nprob, M, blocks, st);
+  else if (best == 1)
+    run_gemm_sp<2, 3, 2, 2, 2, 8>(b, nprob, M, blocks, st);
+  else if (best == 2)
+    run_gemm_sp<2, 3, 2, 1, 4, 8>(b, nprob, M, blocks, st);
+  else if (best == 3)
+    run_gemm_sp<2, 3, 1, 1, 8, 16>(b, nprob, M, blocks, st);
+  else
+    run_gemm_sp<1, 3, 1, 1, 8, 16>(b, nprob, M, blocks, st);
   return hipGetLastError();
 }
 
