@@ -11,8 +11,9 @@ sentences of length U{10..50} (padded to 50), fp32, seeded synthetic weights.
 Prints ONE JSON line.  ``value`` is scored hypothesis-words per second
 (rows / step time) with every input already resident in device memory.
 ``roofline`` reports the vocabulary-projection kernel (75% of the step's
-flops) against the fp32 MFMA peak, from its own HIP-event duration measured
-inside the timed region.  ``cpu_baseline`` times the fp64 oracle on a
+flops) against the matrix cores' peak in the form the kernel runs (fp32
+products: three fp16 MFMAs each, a third of the fp16 peak), from its own
+HIP-event duration measured inside the timed region.  ``cpu_baseline`` times the fp64 oracle on a
 bounded row sample on the host cores.
 
   python bench.py [--steps K] [--warmup W] [--config NAME] [--no-cpu-baseline]
@@ -38,24 +39,28 @@ sys.path.insert(0, ROOT)
 
 METRIC = "scored hypothesis-words/sec at V=100k, H=1024, B=2000; MFMA util %"
 UNIT = "scored hypothesis-words/s"
-PEAK_TFLOPS = {"f32": 157.3, "bf16": 2516.6}   # MI355X dense MFMA
+# MI355X dense MFMA: fp32 products are three fp16 ones (hi and lo halves; the
+# fp32 MFMA's own peak is 157.3), bf16 products one.
+PEAK_TFLOPS = {"f32": 2516.6 / 3, "bf16": 2516.6}
+VOCAB_KERNEL = {"f32": "k_vocab_sp", "bf16": "k_vocab_lse"}
 PEAK_HBM_GBS = 8000.0
 KERNEL_HEADERS = ("paper_1605_04809_amd/csrc/device.hpp", "paper_1605_04809_amd/csrc/internal.hpp")
-KERNEL_FILE = "paper_1605_04809_amd/csrc/kernels.hip"
-VOCAB_SECTION = ("// ------------------------------------------------ vocabulary projection",
-                 "// ---------------------------------------------------- partials combine")
+VOCAB_SECTION = "// ------------------------------------------------ vocabulary projection"
+VOCAB_SOURCES = (("paper_1605_04809_amd/csrc/kernels.hip",
+                  "// ---------------------------------------------------- partials combine"),
+                 ("paper_1605_04809_amd/csrc/split.hip", None))   # each file's section, up to a line or the end
 TRAFFIC_FILE = "profiles/vocab_lse_{workload}_traffic.txt"
 
 
 def kernel_source_hash() -> str:
-    """Hash of the vocabulary kernel's source section and the shared headers."""
+    """Hash of the vocabulary kernels' source sections and the shared headers."""
     h = hashlib.sha256()
     for f in KERNEL_HEADERS:
         with open(os.path.join(ROOT, f), "rb") as fh:
             h.update(fh.read())
-    text = open(os.path.join(ROOT, KERNEL_FILE)).read()
-    a, b = text.index(VOCAB_SECTION[0]), text.index(VOCAB_SECTION[1])
-    h.update(text[a:b].encode())
+    for f, end in VOCAB_SOURCES:
+        text = open(os.path.join(ROOT, f)).read()
+        h.update(text[text.index(VOCAB_SECTION):text.index(end) if end else None].encode())
     return h.hexdigest()[:16]
 
 
@@ -577,7 +582,7 @@ def bench_workload(name, args, cpu_seconds, headline=False):
         "config": {"workload": cfg.name, "V": cfg.V, "E": cfg.E, "H": cfg.H, "A": cfg.A,
                    "S": cfg.S, "src_len": f"U{{{cfg.len_lo}..{cfg.len_hi}}}", "Tpad": cfg.Tpad,
                    "weights": cfg.wtype, "rows_per_step": rows_per_level},
-        "roofline": {"bound": "mfma", "kernel": "k_vocab_lse", "achieved": achieved, "peak": peak,
+        "roofline": {"bound": "mfma", "kernel": VOCAB_KERNEL[cfg.wtype], "achieved": achieved, "peak": peak,
                      "unit": "TFLOP/s", "frac": achieved / peak,
                      "traffic": read_traffic(cfg.name), "algorithmic_flops_per_step": vocab_flops,
                      "launches_per_step": calls_per_step, "avg_launch_ms": vocab_ms / calls_per_step},

@@ -105,7 +105,11 @@ typedef struct {
  * target embeddings times the first GRU's input weights [V x 3H] and times
  * the readout's word weights [V x E] (fp32, computed here: 1.4 GB at V =
  * 100k, H = 1024, E = 500), which the step reads in place of those
- * products.  The caller keeps ownership of the host arrays and may free them
+ * products, and, beside the fp32 matrices, copies of them as two fp16 halves
+ * per value (the same bytes again), which the matrix cores multiply with
+ * fp32's precision (a model whose weights span too wide a range for the
+ * halves keeps the fp32 matrix instructions).  The caller keeps ownership of
+ * the host arrays and may free them
  * on return.  Synchronous.  Errors: NMT_EINVAL (bad dims or null weight),
  * NMT_ENOMEM, NMT_EDEVICE. */
 nmt_status nmt_model_create(const nmt_dims* dims, const nmt_weights* w, nmt_model** out);
@@ -142,7 +146,9 @@ nmt_status nmt_source_from_annotations(nmt_model* m, int32_t S, int32_t Tpad, co
 nmt_status nmt_source_info(const nmt_source* src, int32_t* S, int32_t* Tpad, const float** d_ctx,
                            const float** d_pctx);
 
-/* Free a source (waits for the device first).  NULL is a no-op. */
+/* Free a source (waits for the device first).  NULL is a no-op.  The model
+ * keeps the memory of up to 1 GiB of destroyed sources for the next ones; it
+ * is freed with the model, and when an allocation of the library fails. */
 void nmt_source_destroy(nmt_source* src);
 
 /* Bytes of device workspace that serve nmt_score_batch (and
@@ -395,7 +401,8 @@ nmt_status nmt_score_ensemble(int32_t K, nmt_model* const* models, const nmt_sou
 
 /* Wait for `stream`, then report and clear the model's device error flag:
  * NMT_ERANGE if any call since the last check met an out-of-range id,
- * NMT_EDEVICE on a HIP error, else NMT_OK. */
+ * NMT_EDEVICE on a HIP error or if a source's encoding gave up waiting on
+ * the device (its annotations are then not valid), else NMT_OK. */
 nmt_status nmt_stream_status(nmt_model* m, void* stream);
 
 /* Message for the last failed call on this thread ("" if none). */

@@ -21,7 +21,8 @@ extern "C" {
  * succeed and every one after them fails as out of memory, until the next
  * call; fail_after < 0: no injected failures (the default).  Process-wide,
  * not thread-safe against concurrent library calls.  Returns the number of
- * the library's device allocations alive at the time of the call. */
+ * the library's device allocations alive at the time of the call (memory
+ * that a model keeps of destroyed sources is not counted). */
 int64_t nmt_debug_alloc_hook(int32_t fail_after);
 
 /* The kernel form of the bf16 products of Section 5.1's decoder step (the

@@ -24,6 +24,12 @@
 //   k_key_factors  the keys' factors 2^{2 log2(e) pctx} the attention
 //                  scores read, and each sentence's flag for keys too
 //                  large for them (formed once per source).
+//   k_step_small   a small fp32 model's step up to the readout, one kernel.
+//
+// fp32 models' products run on the fp16 matrix cores where their weights'
+// range allows it (split.hip: k_gemm_sp from 256 hidden units, k_vocab_sp),
+// and the encoder's recurrence runs as one launch (encode.hip); the fp32
+// forms here serve the rest.
 #include <algorithm>
 #include <type_traits>
 
