@@ -71,29 +71,15 @@ __device__ __forceinline__ void split8(const f32x4& x0, const f32x4& x1, float s
 // --------------------------------------------------------- packing
 
 // Largest magnitude of each packed column (bits of |w|, so inf and NaN sort
-// above every finite value), from W [Kpad/4][Npad][4], rows below K.  16 waves
-// share the rows of 64 columns (one thread per column, its loads one after
-// another, took 190 us a matrix on average at the paper's sizes; 14 us here).
-__global__ __launch_bounds__(1024) void k_column_max(const f32x4* __restrict__ W, int64_t Npad, int K,
-                                                     uint32_t* __restrict__ out) {
-  __shared__ uint32_t part[16][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t n = (int64_t)blockIdx.x * 64 + lane;
+// above every finite value), from W [Kpad/4][Npad][4], rows below Krows.
+__global__ void k_column_max(const float* __restrict__ W, int64_t Npad, int K, uint32_t* __restrict__ out) {
+  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (n >= Npad) return;
   uint32_t m = 0;
-  if (n < Npad)
-    for (int v = wave; 4 * v < K; v += 16) {
-      const f32x4 x = W[(int64_t)v * Npad + n];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t b = __builtin_bit_cast(uint32_t, x[e]) & 0x7fffffffu;
-        if (4 * v + e < K && b > m) m = b;
-      }
-    }
-  part[wave][lane] = m;
-  __syncthreads();
-  if (wave != 0 || n >= Npad) return;
-#pragma unroll
-  for (int w = 1; w < 16; ++w) m = part[w][lane] > m ? part[w][lane] : m;
+  for (int k = 0; k < K; ++k) {
+    const uint32_t b = __builtin_bit_cast(uint32_t, W[((int64_t)(k / 4) * Npad + n) * 4 + k % 4]) & 0x7fffffffu;
+    m = b > m ? b : m;
+  }
   out[n] = m;
 }
 
@@ -116,7 +102,7 @@ __global__ void k_row_max(const float* __restrict__ x, int64_t rows, int E, uint
 }
 
 hipError_t launch_magnitudes(const Packed& W, int K, uint32_t* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_column_max, dim3(ceil_div(W.Npad, 64)), dim3(1024), 0, st, (const f32x4*)W.d, W.Npad, K, out);
+  hipLaunchKernelGGL(k_column_max, dim3(ceil_div(W.Npad, 64)), dim3(64), 0, st, (const float*)W.d, W.Npad, K, out);
   return hipGetLastError();
 }
 hipError_t launch_row_magnitudes(const float* x, int64_t rows, int E, uint32_t* out, hipStream_t st) {
