@@ -138,8 +138,9 @@ int64_t split_bytes(int64_t blocks, int steps) { return blocks * steps * 2048; }
 // Block b, step s of the split copy.  gru_hb > 0: the source's packed column
 // tiles hold [r | z | n] of gru_hb units, the copy's blocks r, z, n of 32.
 __global__ __launch_bounds__(256) void k_split_pack(const float* __restrict__ W, int64_t Npad, int K, int steps,
-                                                    int gru_hb, float scale, char* __restrict__ out) {
+                                                    int gru_hb, float scale, char* __restrict__ out, int64_t n_all) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // (block, step, half, column)
+  if (i >= n_all) return;  // (six steps of an odd number of blocks: half a thread block too many)
   const int col = (int)(i & 31), h = (int)(i >> 5) & 1;
   const int64_t bs = i >> 6;
   const int s = (int)(bs % steps);
@@ -166,7 +167,7 @@ hipError_t launch_split_pack(const Packed& W, int K, int steps, int64_t blocks, 
                              hipStream_t st) {
   const int64_t n = blocks * steps * 64;
   hipLaunchKernelGGL(k_split_pack, dim3((unsigned)(n / 256 + (n % 256 != 0))), dim3(256), 0, st, (const float*)W.d,
-                     W.Npad, K, steps, gru_hb, std::ldexp(1.f, scale), (char*)out);
+                     W.Npad, K, steps, gru_hb, std::ldexp(1.f, scale), (char*)out, n);
   return hipGetLastError();
 }
 
