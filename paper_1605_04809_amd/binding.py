@@ -39,7 +39,7 @@ EXPORTS = ("nmt_model_create", "nmt_model_destroy", "nmt_encode", "nmt_source_fr
            "nmt_forest_destroy", "nmt_model_average", "nmt_ensemble_workspace_bytes", "nmt_score_ensemble",
            "nmt_rescorer_create", "nmt_rescore_stack", "nmt_rescorer_info", "nmt_rescorer_destroy",
            "nmt_debug_alloc_hook", "nmt_debug_gemm_form", "nmt_debug_gemm_streamed", "nmt_debug_precompute",
-           "nmt_debug_small_step")
+           "nmt_debug_small_step", "nmt_debug_encode_form")
 
 PHASES = ("gru1", "query", "attention", "gru2", "readout", "vocab", "combine")
 
@@ -124,6 +124,8 @@ def load_library(path: str = LIB_PATH):
     lib.nmt_debug_gemm_streamed.restype = ctypes.c_int64
     lib.nmt_debug_small_step.argtypes = [_I32]
     lib.nmt_debug_small_step.restype = _I32
+    lib.nmt_debug_encode_form.argtypes = [_I32]
+    lib.nmt_debug_encode_form.restype = _I32
     lib.nmt_debug_precompute.argtypes = [_I32]
     lib.nmt_debug_precompute.restype = _I32
     lib.nmt_last_error.argtypes = []
@@ -171,6 +173,12 @@ def debug_small_step(on: int) -> int:
     the readout as one kernel (1, the default) or as the separate ones (0);
     returns the previous setting."""
     return int(load_library().nmt_debug_small_step(on))
+
+
+def debug_encode_form(form: int) -> int:
+    """Test hook (nmt_debug.h): the encoder's recurrence as one launch (1, the
+    default) or a chain of launches (0); returns the previous setting."""
+    return int(load_library().nmt_debug_encode_form(form))
 
 
 def last_error() -> str:

@@ -33,6 +33,7 @@ std::atomic<int64_t> g_alloc_budget{-1};
 std::atomic<int64_t> g_live_allocs{0};
 std::atomic<int32_t> g_precompute{1};  // nmt_debug_precompute
 std::atomic<int32_t> g_small_step{1};  // nmt_debug_small_step
+std::atomic<int32_t> g_encode_form{1};  // nmt_debug_encode_form
 
 nmt_status fail(nmt_status st, const char* fmt, ...) {
   char buf[512];
@@ -694,11 +695,14 @@ nmt_status new_source(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* h_le
                o_kbig = part(S * sizeof(int32_t));
   size_t o_scratch = 0, o_words = 0, o_part = 0, words = 0;
   if (with_scratch) {
-    words = m->coop && m->scan_W ? scan_words_bytes(S, Tpad, d.H, m->bf16, m->cus) : 0;
-    src->enc_ks = words > 0 ? 1 : encoder_ksplit(m, S);
+    src->enc_ks = encoder_ksplit(m, S);
+    words = m->coop && m->scan_W && g_encode_form.load() != 0
+                ? scan_words_bytes(S, Tpad, d.H, m->bf16, src->enc_ks, m->cus)
+                : 0;
     o_scratch = part(rows * 6 * d.H * sizeof(float));
-    o_words = part(words);
-    o_part = part(src->enc_ks > 1 ? (size_t)2 * src->enc_ks * S * 4 * d.H * sizeof(float) : 0);
+    // the one launch's words or the chain's sums: never both
+    o_words = o_part =
+        part(std::max(words, src->enc_ks > 1 ? (size_t)2 * src->enc_ks * S * 4 * d.H * sizeof(float) : (size_t)0));
   }
   src->pool = m->pool;
   hipError_t e = pooled_malloc(*m->pool, &src->block, off, &src->block_bytes);
@@ -823,6 +827,11 @@ int64_t nmt_debug_gemm_streamed(void) { return nmt::g_gemm_streamed.load(); }
 int32_t nmt_debug_small_step(int32_t on) {
   if (on != 0 && on != 1) return -1;
   return g_small_step.exchange(on);
+}
+
+int32_t nmt_debug_encode_form(int32_t form) {
+  if (form != 0 && form != 1) return -1;
+  return g_encode_form.exchange(form);
 }
 
 int32_t nmt_debug_precompute(int32_t on) {
@@ -1020,8 +1029,8 @@ nmt_status nmt_encode(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* d_sr
     b.brz = m->enc_bias.brz;
     b.bni = m->enc_bias.bni;
     b.bns = m->enc_bias.bns;
-    e = launch_enc_scan(m->scan_W, Xp, src->ctx, src->len, src->words, m->err, b, S, Tpad, H, m->bf16, m->scan_scale,
-                        m->cus, st);
+    e = launch_enc_scan(m->scan_W, Xp, src->ctx, src->len, src->words, m->err, b, S, Tpad, H, m->bf16, src->enc_ks,
+                        m->scan_scale, m->cus, st);
     if (e != hipSuccess) {  // a launch that does not fit the device as it is now: the chain computes it all again
       (void)hipGetLastError();
       e = hipSuccess;

@@ -554,6 +554,16 @@ __device__ __forceinline__ float tanhf_(float x) {
 #endif
 }
 
+// The cell of Section 5.1's GRUs from the gate pre-activations (without
+// biases) and the previous state.
+__device__ __forceinline__ float gru_cell(float sr, float sz, float sni, float sns, float br, float bz, float bni,
+                                          float bns, float xr, float xz, float xn, float hp) {
+  const float rg = sigmoidf_(sr + br + xr);
+  const float zg = sigmoidf_(sz + bz + xz);
+  const float ng = tanhf_(sni + bni + xn + rg * (sns + bns));
+  return zg * hp + (1.f - zg) * ng;
+}
+
 // Row of accumulator register r for lane half h.
 __device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 

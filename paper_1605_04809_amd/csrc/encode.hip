@@ -10,6 +10,12 @@
 // eighth of K), computes them for up to 32 sentences per position, and hands
 // the new states to the other blocks through memory.
 //
+// Which wave sums which steps.  fp32: eight runs of equal length.  bf16: the
+// chain of launches' K splits, one to a wave, so that every sum has the
+// chain's terms in the chain's order and the states are the chain's bit for
+// bit (a 16x16x32 MFMA adds like two 32x32x16 ones): a state that rounds to
+// bf16 the other way would travel through the rest of the sentence.
+//
 // Handing over.  The states of a position travel as 8-byte words (two units'
 // halves, or four bf16 units) in the MFMA's operand order, written and read
 // by relaxed device-scope atomics.  Every word starts as all ones, a NaN
@@ -37,7 +43,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kScanUnits = 16;   // hidden units per block
 constexpr int kScanRows = 32;    // sentences per block
-constexpr int kScanWaveK = 4;    // 32-k steps per wave, at most
 constexpr int kScanPolls = 1 << 18;
 constexpr uint64_t kNotYet = ~0ull;
 
@@ -88,10 +93,17 @@ struct ScanArgs {
   int* err;
   const float *brz, *bni, *bns;
   int32_t S, Tpad, H, nks;
+  int32_t splits;    // waves that share the steps
   float hscale, inv;
 };
 
-template <bool BF16>
+// The first step of wave w's run: fp32 an equal share; bf16 that of K split w
+// of the chain, which splits chunks of two steps.
+__host__ __device__ inline int scan_first(bool bf16, int nks, int splits, int w) {
+  return bf16 ? min(2 * ((nks + 1) / 2 * w / splits), nks) : min((nks + splits - 1) / splits * w, nks);
+}
+
+template <bool BF16, int WK>  // WK: 32-k steps per wave, at most
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_enc_scan(ScanArgs a) {
   constexpr int NPL = BF16 ? 1 : 2;         // planes of a weight fragment
   constexpr int NA = BF16 ? 2 : 4;          // words per lane and step
@@ -105,16 +117,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   const int nrt = rows > 16 ? 2 : 1;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 
-  // this wave's weights: steps wave, wave + 8, ...
-  f32x4 w[3][kScanWaveK][NPL];
+  // this wave's weights: steps s0 .. s1 - 1
+  const int s0 = wave < a.splits ? scan_first(BF16, nks, a.splits, wave) : nks;
+  const int s1 = wave < a.splits ? scan_first(BF16, nks, a.splits, wave + 1) : nks;
+  f32x4 w[3][WK][NPL];
 #pragma unroll
-  for (int i = 0; i < kScanWaveK; ++i) {
-    const int s = wave + 8 * i;
+  for (int i = 0; i < WK; ++i) {
+    const int s = s0 + i;
 #pragma unroll
     for (int g = 0; g < 3; ++g)
 #pragma unroll
       for (int p = 0; p < NPL; ++p)
-        w[g][i][p] = s < nks ? a.W[(((((int64_t)dir * nub + ub) * 3 + g) * nks + s) * NPL + p) * 64 + lane] : zero4();
+        w[g][i][p] = s < s1 ? a.W[(((((int64_t)dir * nub + ub) * 3 + g) * nks + s) * NPL + p) * 64 + lane] : zero4();
   }
 
   // the cell: thread tid owns UPT units of one sentence
@@ -160,26 +174,26 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
         // read another word of the tile and count as zeros (units past H
         // meet zero weights)
         const uint64_t* tsrc = src + rt * tile_words;
-        int off[kScanWaveK][NA];
-        uint64_t x[kScanWaveK][NA];
+        int off[WK][NA];
+        uint64_t x[WK][NA];
 #pragma unroll
-        for (int i = 0; i < kScanWaveK; ++i)
+        for (int i = 0; i < WK; ++i)
 #pragma unroll
           for (int q = 0; q < NA; ++q) {
-            const int s = wave + 8 * i;
-            off[i][q] = live && s * 32 + 8 * (lane >> 4) + q * UPT < H ? (s * NA + q) * 64 + lane : -1;
+            const int s = s0 + i;
+            off[i][q] = live && s < s1 && s * 32 + 8 * (lane >> 4) + q * UPT < H ? (s * NA + q) * 64 + lane : -1;
           }
         for (int polls = 0;; ++polls) {
           bool ok = true;
 #pragma unroll
-          for (int i = 0; i < kScanWaveK; ++i)
+          for (int i = 0; i < WK; ++i)
 #pragma unroll
             for (int q = 0; q < NA; ++q)
               x[i][q] = __hip_atomic_load(
                   (const uint64_t*)((const char*)tsrc + (uint32_t)(off[i][q] >= 0 ? off[i][q] * 8 : 0)), __ATOMIC_RELAXED,
                   __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-          for (int i = 0; i < kScanWaveK; ++i)
+          for (int i = 0; i < WK; ++i)
 #pragma unroll
             for (int q = 0; q < NA; ++q) ok = ok && (off[i][q] < 0 || x[i][q] != kNotYet);
           if (__builtin_amdgcn_ballot_w64(!ok) == 0 || !waiting) break;
@@ -194,7 +208,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
           __builtin_amdgcn_s_sleep(16);
         }
 #pragma unroll
-        for (int i = 0; i < kScanWaveK; ++i) {
+        for (int i = 0; i < WK; ++i) {
 #pragma unroll
           for (int q = 0; q < NA; ++q) x[i][q] = off[i][q] < 0 ? 0 : x[i][q];
           typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -235,10 +249,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
       fu o;
 #pragma unroll
       for (int e = 0; e < UPT; ++e) {
-        const float rg = sigmoidf_(sr[e] * a.inv + br[e] + xr[e]);
-        const float zg = sigmoidf_(sz[e] * a.inv + bz[e] + xz[e]);
-        const float ng = tanhf_(bni[e] + xn[e] + rg * (sn[e] * a.inv + bns[e]));
-        const float hn = zg * hp[e] + (1.f - zg) * ng;
+        const float inv = BF16 ? 1.f : a.inv;
+        const float hn = gru_cell(sr[e] * inv, sz[e] * inv, 0.f, sn[e] * inv, br[e], bz[e], bni[e], bns[e], xr[e], xz[e],
+                                  xn[e], hp[e]);
         o[e] = pos < L ? hn : 0.f;
       }
       hp = o;
@@ -287,8 +300,20 @@ hipError_t launch_scan_pack(const Packed (&U)[2], int H, bool bf16, int hb, int 
 // Sentences per launch: as many groups of 32 as are resident at once, at most two.
 static int scan_groups(int H, int cus) { return std::min(2, cus / (2 * scan_blocks(H))); }
 
-size_t scan_words_bytes(int S, int Tpad, int H, bool bf16, int cus) {
-  if (H > 32 * 8 * kScanWaveK) return 0;
+// Waves that share K, and the steps that the longest run of one has.  fp32 weights take twice the registers, so four
+// steps a wave (H of at most 1,024) against eight.
+constexpr int kScanMaxH = 1024, kScanLongF32 = 4, kScanLongBF16 = 8;
+static int scan_splits(bool bf16, int chain_ks) { return bf16 ? chain_ks : 8; }
+static int scan_longest(int H, bool bf16, int splits) {
+  int n = 0;
+  for (int w = 0; w < splits; ++w)
+    n = std::max(n, scan_first(bf16, scan_steps(H), splits, w + 1) - scan_first(bf16, scan_steps(H), splits, w));
+  return n;
+}
+
+size_t scan_words_bytes(int S, int Tpad, int H, bool bf16, int chain_ks, int cus) {
+  const int splits = scan_splits(bf16, chain_ks);
+  if (H > kScanMaxH || splits > 8 || scan_longest(H, bf16, splits) > (bf16 ? kScanLongBF16 : kScanLongF32)) return 0;
   const int g = scan_groups(H, cus);
   if (g < 1 || S > 4 * kScanRows) return 0;  // more sentences fill the chip as a chain of launches
   const size_t n = (size_t)Tpad * 2 * std::min(g, ceil_div(S, kScanRows)) * 2 * scan_steps(H) * (bf16 ? 2 : 4) * 512;
@@ -296,10 +321,15 @@ size_t scan_words_bytes(int S, int Tpad, int H, bool bf16, int cus) {
 }
 
 hipError_t launch_enc_scan(const void* W, const float* xp, float* ctx, const int32_t* len, void* words, int* err,
-                           const GruEpi& bias, int S, int Tpad, int H, bool bf16, int scale, int cus, hipStream_t st) {
+                           const GruEpi& bias, int S, int Tpad, int H, bool bf16, int chain_ks, int scale, int cus,
+                           hipStream_t st) {
   const int g = scan_groups(H, cus), per = std::min(g, ceil_div(S, kScanRows)) * kScanRows;
-  const int64_t bytes = (int64_t)scan_words_bytes(S, Tpad, H, bf16, cus);
+  const int64_t bytes = (int64_t)scan_words_bytes(S, Tpad, H, bf16, chain_ks, cus);
   if (bytes <= 0) return hipErrorInvalidValue;
+  const int splits = scan_splits(bf16, chain_ks);
+  const void* kernel = !bf16 ? (const void*)k_enc_scan<false, kScanLongF32>
+                             : (scan_longest(H, bf16, splits) <= 4 ? (const void*)k_enc_scan<true, 4>
+                                                                   : (const void*)k_enc_scan<true, kScanLongBF16>);
   for (int s0 = 0; s0 < S; s0 += per) {
     hipLaunchKernelGGL(k_fill_words, dim3(ceil_div(bytes / 16, 256)), dim3(256), 0, st, (uint64_t*)words, bytes / 16);
     ScanArgs a{};
@@ -316,13 +346,12 @@ hipError_t launch_enc_scan(const void* W, const float* xp, float* ctx, const int
     a.Tpad = Tpad;
     a.H = H;
     a.nks = scan_steps(H);
+    a.splits = splits;
     a.hscale = std::ldexp(1.f, kSplitState);
     a.inv = bf16 ? 1.f : std::ldexp(1.f, -(kSplitState + scale));
     void* args[] = {&a};
     const dim3 grid(scan_blocks(H), 2, ceil_div(a.S, kScanRows));
-    const hipError_t e =
-        hipLaunchCooperativeKernel(bf16 ? (const void*)k_enc_scan<true> : (const void*)k_enc_scan<false>, grid,
-                                   dim3(512), args, 0, st);
+    const hipError_t e = hipLaunchCooperativeKernel(kernel, grid, dim3(512), args, 0, st);
     if (e != hipSuccess) return e;
   }
   return hipGetLastError();

@@ -256,16 +256,6 @@ struct GruBatch {
   int32_t part_M;  // rows of each problem's part block
 };
 
-// The cell of Section 5.1's GRUs from the gate pre-activations (without
-// biases) and the previous state.
-__device__ __forceinline__ float gru_cell(float sr, float sz, float sni, float sns, float br, float bz, float bni,
-                                          float bns, float xr, float xz, float xn, float hp) {
-  const float rg = sigmoidf_(sr + br + xr);
-  const float zg = sigmoidf_(sz + bz + xz);
-  const float ng = tanhf_(sni + bni + xn + rg * (sns + bns));
-  return zg * hp + (1.f - zg) * ng;
-}
-
 // SPLIT: the block sums only its split's share of the K chunks (of all A
 // segments together) and writes the raw sums to batch.part; k_gru_cell adds
 // the splits in order and applies the cell.  For launches with few row

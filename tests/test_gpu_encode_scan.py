@@ -52,6 +52,34 @@ def test_annotations_keys_and_states_match_the_oracle(kw, wtype):
     g.close()
 
 
+# The chain's K splits at S of at most 64 and more: one of a few steps, seven with a longer last one, eight, four of
+# eight steps; a last step and a last chunk that are not full; position and mask edges.
+@pytest.mark.parametrize("kw", [dict(S=1, H=1024), dict(S=20, H=1024), dict(S=64, H=960), dict(S=65, H=1024),
+                                dict(S=128, H=1000), dict(S=7, H=64), dict(S=7, H=100), dict(S=9, H=192),
+                                dict(S=33, H=320), dict(S=5, H=36), dict(S=90, H=896), dict(S=70, H=704),
+                                dict(S=40, H=512, Tpad=40, len_hi=40)],
+                         ids=lambda kw: "_".join(f"{k}{v}" for k, v in kw.items()))
+def test_bf16_states_are_the_chains_bit_for_bit(kw):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_cases
+    from paper_1605_04809_amd import binding as nb
+    wl = unit_gain(BASE.replace(wtype="bf16", **kw))
+    g = gpu_cases.GpuRun(wl)
+    one = [x.cpu().numpy() for x in g.src.copy_out()] + [g.s0.cpu().numpy()]
+    prev = nb.debug_encode_form(0)
+    try:
+        c = gpu_cases.GpuRun(wl, model=g.model)
+    finally:
+        nb.debug_encode_form(prev)
+    chain = [x.cpu().numpy() for x in c.src.copy_out()] + [c.s0.cpu().numpy()]
+    for name, a, b in zip(("ctx", "pctx", "s0"), one, chain):
+        np.testing.assert_array_equal(a.view(np.int32), b.view(np.int32), err_msg=name)
+    c.src.close()
+    g.close()
+
+
 def test_sources_on_two_streams_at_once():
     """Two recurrences in flight together give what each gives alone."""
     torch = pytest.importorskip("torch")
