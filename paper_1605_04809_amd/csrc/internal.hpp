@@ -6,7 +6,6 @@
 #include <stdint.h>
 
 #include <atomic>
-#include <vector>
 
 #include "device.hpp"
 
@@ -293,14 +292,21 @@ constexpr int kNoSplit = 1 << 20;
 // 43.4 us a step against 44.4), and at H of at most 128 one kernel.
 constexpr int kSplitMinH = 256;
 static_assert(kSplitMinH >= kSpLongK, "the GRU tiles take a long K");
-// bits of the largest magnitude of each packed column of W's first K rows
-// (out [Npad]), or of each row of x [rows x E]
-hipError_t launch_magnitudes(const Packed& W, int K, uint32_t* out, hipStream_t st);
-hipError_t launch_row_magnitudes(const float* x, int64_t rows, int E, uint32_t* out, hipStream_t st);
-// The scale exponent for a matrix with these column (or row) magnitudes, or
-// kNoSplit where the halves would hold some column less precisely than fp32
-// (see split.hip) or a value is not finite.
-int split_scale(const std::vector<uint32_t>& mags);
+// Range of a matrix's column (or a table's row) magnitudes: bits of the
+// largest, and of the smallest that is not zero (~0u if there is none), over
+// packed columns of W's first K rows, rows of x [rows x E], or the finite
+// values of the bias row; each adds to *out, which launch_no_range empties.
+struct MagRange {
+  uint32_t most, least;
+};
+hipError_t launch_no_range(MagRange* r, int n, hipStream_t st);
+hipError_t launch_column_range(const Packed& W, int K, MagRange* out, hipStream_t st);
+hipError_t launch_row_range(const float* x, int64_t rows, int E, MagRange* out, hipStream_t st);
+hipError_t launch_bias_range(const Packed& W, MagRange* out, hipStream_t st);
+// The scale exponent for a matrix of this range, or kNoSplit where the halves
+// would hold some column (or row) less precisely than fp32 (see split.hip) or
+// a value is not finite.
+int split_scale(MagRange r);
 int split_steps(int K, bool vocab);
 int64_t split_bytes(int64_t blocks, int steps);
 hipError_t launch_split_pack(const Packed& W, int K, int steps, int64_t blocks, int gru_hb, int scale, void* out,

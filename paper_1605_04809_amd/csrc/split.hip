@@ -70,57 +70,127 @@ __device__ __forceinline__ void split8(const f32x4& x0, const f32x4& x1, float s
 
 // --------------------------------------------------------- packing
 
-// Largest magnitude of each packed column (bits of |w|, so inf and NaN sort
-// above every finite value), from W [Kpad/4][Npad][4], rows below Krows.
-__global__ void k_column_max(const float* __restrict__ W, int64_t Npad, int K, uint32_t* __restrict__ out) {
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= Npad) return;
-  uint32_t m = 0;
-  for (int k = 0; k < K; ++k) {
-    const uint32_t b = __builtin_bit_cast(uint32_t, W[((int64_t)(k / 4) * Npad + n) * 4 + k % 4]) & 0x7fffffffu;
-    m = b > m ? b : m;
-  }
-  out[n] = m;
-}
-
-// Largest magnitude of each row of a row-major [rows x E] table.
-__global__ void k_row_max(const float* __restrict__ x, int64_t rows, int E, uint32_t* __restrict__ out) {
-  const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64;
-  const int lane = threadIdx.x & 63;
-  if (r >= rows) return;
-  uint32_t m = 0;
-  for (int k = lane; k < E; k += 64) {
-    const uint32_t b = __builtin_bit_cast(uint32_t, x[r * E + k]) & 0x7fffffffu;
-    m = b > m ? b : m;
-  }
+// A wave's share of a matrix's range: the largest of its lanes' magnitudes
+// (bits of |x|, so inf and NaN sort above every finite value) and the
+// smallest that is not zero.
+__device__ __forceinline__ void add_range(uint32_t m, MagRange* __restrict__ r) {
+  uint32_t most = m, least = m ? m : ~0u;
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
-    const uint32_t y = __shfl_xor(m, o, 64);
-    m = y > m ? y : m;
+    most = max(most, (uint32_t)__shfl_xor(most, o, 64));
+    least = min(least, (uint32_t)__shfl_xor(least, o, 64));
   }
-  if (lane == 0) out[r] = m;
+  if ((threadIdx.x & 63) == 0 && most) {
+    atomicMax(&r->most, most);
+    atomicMin(&r->least, least);
+  }
 }
 
-hipError_t launch_magnitudes(const Packed& W, int K, uint32_t* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_column_max, dim3(ceil_div(W.Npad, 64)), dim3(64), 0, st, (const float*)W.d, W.Npad, K, out);
+// The largest magnitude of a vector's first n elements.  (Each element goes
+// through a float of its own: __builtin_bit_cast of a vector's element takes
+// the vector's first element whatever the index.)
+__device__ __forceinline__ uint32_t vec_magnitude(const f32x4& x, int n) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float f = x[e];
+    const uint32_t b = __builtin_bit_cast(uint32_t, f) & 0x7fffffffu;
+    m = e < n ? max(m, b) : m;
+  }
+  return m;
+}
+
+// Range of the packed columns' largest magnitudes over W's first K rows, W
+// [Kpad/4][Npad][4].  16 waves share the rows of 64 columns: one thread per
+// column, its loads one after another, took 190 us a matrix on average over a
+// model's matrices at the paper's sizes.
+__global__ __launch_bounds__(1024) void k_column_range(const f32x4* __restrict__ W, int64_t Npad, int K,
+                                                       MagRange* __restrict__ out) {
+  __shared__ uint32_t part[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t n = (int64_t)blockIdx.x * 64 + lane;
+  uint32_t m = 0;
+  if (n < Npad)
+    for (int v = wave; 4 * v < K; v += 16) m = max(m, vec_magnitude(W[(int64_t)v * Npad + n], K - 4 * v));
+  part[wave][lane] = m;
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int w = 1; w < 16; ++w) m = max(m, part[w][lane]);
+  add_range(m, out);
+}
+
+// The same of the rows of a row-major [rows x E] table, E a multiple of 4: a
+// wave takes every (16 gridDim.x)-th row and keeps its lanes' largest, then
+// smallest, row.
+__global__ __launch_bounds__(1024) void k_row_range(const float* __restrict__ x, int64_t rows, int E,
+                                                    MagRange* __restrict__ out) {
+  __shared__ uint32_t most_s[16], least_s[16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t most = 0, least = ~0u;
+  for (int64_t r = (int64_t)blockIdx.x * 16 + wave; r < rows; r += (int64_t)gridDim.x * 16) {
+    uint32_t m = 0;
+    for (int k = 4 * lane; k < E; k += 256) m = max(m, vec_magnitude(*(const f32x4*)(x + r * E + k), 4));
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) m = max(m, (uint32_t)__shfl_xor(m, o, 64));
+    most = max(most, m);
+    if (m) least = min(least, m);
+  }
+  if (lane == 0) {
+    most_s[wave] = most;
+    least_s[wave] = least;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int w = 1; w < 16; ++w) {
+    most = max(most, most_s[w]);
+    least = min(least, least_s[w]);
+  }
+  if (most) {
+    atomicMax(&out->most, most);
+    atomicMin(&out->least, least);
+  }
+}
+
+// Range of the finite magnitudes of packed row krow (the output bias).
+__global__ __launch_bounds__(256) void k_bias_range(const float* __restrict__ W, int64_t Npad, int krow,
+                                                    MagRange* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const float f = i < Npad ? W[((int64_t)(krow / 4) * Npad + i) * 4 + krow % 4] : 0.f;
+  const uint32_t b = __builtin_bit_cast(uint32_t, f) & 0x7fffffffu;
+  add_range(b < 0x7f800000u ? b : 0, out);
+}
+
+__global__ void k_no_range(MagRange* __restrict__ r, int n) {
+  if ((int)threadIdx.x < n) r[threadIdx.x] = MagRange{0, ~0u};
+}
+
+hipError_t launch_no_range(MagRange* r, int n, hipStream_t st) {
+  if (n > 64) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_no_range, dim3(1), dim3(64), 0, st, r, n);
   return hipGetLastError();
 }
-hipError_t launch_row_magnitudes(const float* x, int64_t rows, int E, uint32_t* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_row_max, dim3(ceil_div(rows, 4)), dim3(256), 0, st, x, rows, E, out);
+hipError_t launch_column_range(const Packed& W, int K, MagRange* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_column_range, dim3(ceil_div(W.Npad, 64)), dim3(1024), 0, st, (const f32x4*)W.d, W.Npad, K, out);
+  return hipGetLastError();
+}
+hipError_t launch_row_range(const float* x, int64_t rows, int E, MagRange* out, hipStream_t st) {
+  const int blocks = (int)std::min<int64_t>((rows + 15) / 16, 2048);
+  hipLaunchKernelGGL(k_row_range, dim3(blocks), dim3(1024), 0, st, x, rows, E, out);
+  return hipGetLastError();
+}
+hipError_t launch_bias_range(const Packed& W, MagRange* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_bias_range, dim3(ceil_div(W.Npad, 256)), dim3(256), 0, st, (const float*)W.d, W.Npad, W.Krows, out);
   return hipGetLastError();
 }
 
-int split_scale(const std::vector<uint32_t>& mags) {
-  uint32_t mx = 0;
-  for (uint32_t m : mags) mx = std::max(mx, m);
-  if (mx >= 0x7f800000u) return kNoSplit;  // inf or NaN
-  if (mx == 0) return 0;
-  const float fmx = __builtin_bit_cast(float, mx);
-  const float least = std::ldexp(fmx, -14);
-  for (uint32_t m : mags)
-    if (m != 0 && __builtin_bit_cast(float, m) < least) return kNoSplit;
+int split_scale(MagRange r) {
+  if (r.most >= 0x7f800000u) return kNoSplit;  // inf or NaN
+  if (r.most == 0) return 0;
+  const float most = __builtin_bit_cast(float, r.most), least = __builtin_bit_cast(float, r.least);
+  if (least < std::ldexp(most, -14)) return kNoSplit;
   int e = 0;
-  (void)std::frexp(fmx, &e);  // fmx = f 2^e, f in [1/2, 1)
+  (void)std::frexp(most, &e);  // most = f 2^e, f in [1/2, 1)
   const int s = 15 - e;
   return (s < -60 || s > 60) ? kNoSplit : s;
 }
