@@ -401,8 +401,7 @@ nmt_status nmt_score_ensemble(int32_t K, nmt_model* const* models, const nmt_sou
 
 /* Wait for `stream`, then report and clear the model's device error flag:
  * NMT_ERANGE if any call since the last check met an out-of-range id,
- * NMT_EDEVICE on a HIP error or if a source's encoding gave up waiting on
- * the device (its annotations are then not valid), else NMT_OK. */
+ * NMT_EDEVICE on a HIP error, else NMT_OK. */
 nmt_status nmt_stream_status(nmt_model* m, void* stream);
 
 /* Message for the last failed call on this thread ("" if none). */

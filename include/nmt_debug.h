@@ -58,10 +58,12 @@ int32_t nmt_debug_precompute(int32_t on);
  * setting, or -1 (and changes nothing) for a value other than 0 or 1. */
 int32_t nmt_debug_small_step(int32_t on);
 
-/* The encoder's recurrence: one launch where it applies (1, the default) or
- * the chain of launches (0), so a test can compare the two, which give the
- * same values with bf16 weights.  Process-wide.  Returns the previous
- * setting, or -1 (and changes nothing) for another value. */
+/* The encoder's recurrence: one launch where it applies (1, the default), the
+ * chain of launches (0), or one launch whose blocks give up waiting for each
+ * other at once (2), so that the kernel for that case computes it, so a test
+ * can compare them: 1 and 2 give the same values, with bf16 weights 0 too.
+ * Process-wide.  Returns the previous setting, or -1 (and changes nothing)
+ * for another value. */
 int32_t nmt_debug_encode_form(int32_t form);
 
 #ifdef __cplusplus

@@ -177,7 +177,8 @@ def debug_small_step(on: int) -> int:
 
 def debug_encode_form(form: int) -> int:
     """Test hook (nmt_debug.h): the encoder's recurrence as one launch (1, the
-    default) or a chain of launches (0); returns the previous setting."""
+    default), a chain of launches (0) or a launch whose waits run out (2);
+    returns the previous setting."""
     return int(load_library().nmt_debug_encode_form(form))
 
 

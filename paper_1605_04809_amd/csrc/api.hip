@@ -231,6 +231,7 @@ struct nmt_source {
   float* gru_part = nullptr;  // encoder: the recurrent GRU's split-K sums [2][enc_ks][S][4H]
   int enc_ks = 1;
   void* words = nullptr;  // encoder: the one-launch recurrence's hand-over words
+  int* gave_up = nullptr;  // and its flag that a wait ran out
   int32_t* len = nullptr;
   std::vector<int32_t> h_len;
 };
@@ -700,7 +701,7 @@ nmt_status new_source(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* h_le
   const size_t o_ctx = part(rows * 2 * d.H * sizeof(float)), o_pctx = part(rows * d.A * sizeof(float)),
                o_kfac = part(rows * d.A * sizeof(float)),
                o_cproj = part(m->precomp ? rows * m->cpw_ld * sizeof(float) : 0), o_len = part(S * sizeof(int32_t)),
-               o_kbig = part(S * sizeof(int32_t));
+               o_kbig = part(S * sizeof(int32_t)), o_gave_up = part(sizeof(int));
   size_t o_scratch = 0, o_words = 0, o_part = 0, words = 0;
   if (with_scratch) {
     src->enc_ks = encoder_ksplit(m, S);
@@ -722,6 +723,7 @@ nmt_status new_source(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* h_le
     if (m->precomp) src->cproj = (float*)(base + o_cproj);
     src->len = (int32_t*)(base + o_len);
     src->kbig = (int32_t*)(base + o_kbig);
+    src->gave_up = (int*)(base + o_gave_up);
     if (with_scratch) src->scratch = (float*)(base + o_scratch);
     if (words > 0) src->words = base + o_words;
     if (src->enc_ks > 1) src->gru_part = (float*)(base + o_part);
@@ -838,7 +840,7 @@ int32_t nmt_debug_small_step(int32_t on) {
 }
 
 int32_t nmt_debug_encode_form(int32_t form) {
-  if (form != 0 && form != 1) return -1;
+  if (form < 0 || form > 2) return -1;
   return g_encode_form.exchange(form);
 }
 
@@ -1037,7 +1039,7 @@ nmt_status nmt_encode(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* d_sr
     b.brz = m->enc_bias.brz;
     b.bni = m->enc_bias.bni;
     b.bns = m->enc_bias.bns;
-    e = launch_enc_scan(m->scan_W, Xp, src->ctx, src->len, src->words, m->err, b, S, Tpad, H, m->bf16, src->enc_ks,
+    e = launch_enc_scan(m->scan_W, Xp, src->ctx, src->len, src->words, src->gave_up, g_encode_form.load(), b, S, Tpad, H, m->bf16, src->enc_ks,
                         m->scan_scale, m->cus, st);
     if (e != hipSuccess) {  // a launch that does not fit the device as it is now: the chain computes it all again
       (void)hipGetLastError();
@@ -1670,7 +1672,6 @@ nmt_status nmt_stream_status(nmt_model* m, void* stream) {
   e = hipMemcpy(&flag, m->err, sizeof(int), hipMemcpyDeviceToHost);
   if (e == hipSuccess && flag) e = hipMemset(m->err, 0, sizeof(int));
   if (e != hipSuccess) return hip_fail(e, "nmt_stream_status");
-  if (flag & 2) return fail(NMT_EDEVICE, "the encoder's blocks did not run together in a call since the last status check");
   if (flag) return fail(NMT_ERANGE, "an id was out of range in a call since the last status check");
   return ok();
 }

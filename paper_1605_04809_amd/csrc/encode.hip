@@ -27,8 +27,10 @@
 //
 // The blocks wait for one another, so all of them must be resident: the
 // kernel is launched cooperatively, which the runtime refuses where they do
-// not fit.  A wait is bounded all the same (kScanPolls); a block that gives
-// up sets the model's error flag and runs on without waiting.
+// not fit.  A wait is bounded all the same (kScanPolls, about a quarter of a
+// second, where another process's kernels hold the CUs); a block that gives
+// up sets a flag and runs on without waiting, and the kernel after it, which
+// needs no other block (k_enc_alone), computes the recurrence again.
 #include <algorithm>
 #include <cmath>
 
@@ -41,6 +43,7 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
+constexpr int kScanMaxH = 1024;
 constexpr int kScanUnits = 16;   // hidden units per block
 constexpr int kScanRows = 32;    // sentences per block
 constexpr int kScanPolls = 1 << 18;
@@ -79,9 +82,10 @@ __global__ __launch_bounds__(256) void k_scan_pack(const void* __restrict__ W, i
   }
 }
 
-__global__ void k_fill_words(uint64_t* __restrict__ p, int64_t n2) {
+__global__ void k_fill_words(uint64_t* __restrict__ p, int64_t n2, int* __restrict__ gave_up) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n2) ((ulong2*)p)[i] = make_ulong2(kNotYet, kNotYet);
+  if (i == 0) *gave_up = 0;
 }
 
 struct ScanArgs {
@@ -90,10 +94,11 @@ struct ScanArgs {
   float* ctx;        // [S x Tpad x 2H]
   const int32_t* len;
   uint64_t* words;   // [Tpad][direction][group][row tile][step][word][lane]
-  int* err;
+  int* gave_up;      // set by a block whose wait ran out
   const float *brz, *bni, *bns;
   int32_t S, Tpad, H, nks;
   int32_t splits;    // waves that share the steps
+  int32_t polls;     // bound of a wait
   float hscale, inv;
 };
 
@@ -103,12 +108,82 @@ __host__ __device__ inline int scan_first(bool bf16, int nks, int splits, int w)
   return bf16 ? min(2 * ((nks + 1) / 2 * w / splits), nks) : min((nks + splits - 1) / splits * w, nks);
 }
 
+template <bool BF16>
+struct Scan {
+  static constexpr int NPL = BF16 ? 1 : 2;  // planes of a weight fragment
+  static constexpr int NA = BF16 ? 2 : 4;   // words per lane and step
+  static constexpr int UPT = BF16 ? 4 : 2;  // units per word
+  typedef float fu __attribute__((ext_vector_type(UPT)));
+
+  // Fragment of gate g, step s, plane p of unit block ub.
+  static __device__ __forceinline__ f32x4 weight(const ScanArgs& a, int dir, int nub, int ub, int g, int s, int p,
+                                                 int lane) {
+    return a.W[(((((int64_t)dir * nub + ub) * 3 + g) * a.nks + s) * NPL + p) * 64 + lane];
+  }
+  // One step's products of the three gates.
+  static __device__ __forceinline__ void step(const f32x4 (&w)[3][NPL], const uint64_t (&x)[NA], f32x4 (&acc)[3]) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    if constexpr (BF16) {
+      const u32x4 v = {(uint32_t)x[0], (uint32_t)(x[0] >> 32), (uint32_t)x[1], (uint32_t)(x[1] >> 32)};
+#pragma unroll
+      for (int g = 0; g < 3; ++g)
+        acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[g][0]),
+                                                         __builtin_bit_cast(bf16x8, v), acc[g], 0, 0, 0);
+    } else {
+      const u32x4 vh = {(uint32_t)x[0], (uint32_t)x[1], (uint32_t)x[2], (uint32_t)x[3]};
+      const u32x4 vl = {(uint32_t)(x[0] >> 32), (uint32_t)(x[1] >> 32), (uint32_t)(x[2] >> 32), (uint32_t)(x[3] >> 32)};
+      const f16x8 hh = __builtin_bit_cast(f16x8, vh), hl = __builtin_bit_cast(f16x8, vl);
+#pragma unroll
+      for (int g = 0; g < 3; ++g) {
+        f32x4& d = acc[g];
+        d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[g][NPL - 1]), hh, d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[g][0]), hl, d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[g][0]), hh, d, 0, 0, 0);
+      }
+    }
+  }
+  // The states of UPT units from their gates' sums.
+  static __device__ __forceinline__ fu cell(const ScanArgs& a, const fu& sr, const fu& sz, const fu& sn, const fu& br,
+                                            const fu& bz, const fu& bni, const fu& bns, const fu& xr, const fu& xz,
+                                            const fu& xn, const fu& hp, bool keep) {
+    fu o;
+#pragma unroll
+    for (int e = 0; e < UPT; ++e) {
+      const float inv = BF16 ? 1.f : a.inv;
+      const float hn = gru_cell(sr[e] * inv, sz[e] * inv, 0.f, sn[e] * inv, br[e], bz[e], bni[e], bns[e], xr[e], xz[e],
+                                xn[e], hp[e]);
+      o[e] = keep ? hn : 0.f;
+    }
+    return o;
+  }
+  // Their word as an operand, never all ones.
+  static __device__ __forceinline__ uint64_t word(const ScanArgs& a, const fu& o) {
+    auto canon = [](float v) { return v == v ? v : __builtin_nanf(""); };
+    uint32_t lo32, hi32;
+    if constexpr (BF16) {
+      const f32x2 c0 = f32x2{canon(o[0]), canon(o[1])}, c1 = f32x2{canon(o[UPT - 2]), canon(o[UPT - 1])};
+      lo32 = __builtin_bit_cast(uint32_t, __builtin_convertvector(c0, bf16x2));
+      hi32 = __builtin_bit_cast(uint32_t, __builtin_convertvector(c1, bf16x2));
+    } else {
+      const f32x2 c0 = f32x2{canon(o[0]) * a.hscale, canon(o[1]) * a.hscale};
+      const f16x2 hi = __builtin_convertvector(c0, f16x2);
+      const f32x2 c1 = f32x2{c0[0] - (float)hi[0], c0[1] - (float)hi[1]};
+      lo32 = __builtin_bit_cast(uint32_t, hi);
+      hi32 = __builtin_bit_cast(uint32_t, __builtin_convertvector(c1, f16x2));
+    }
+    return (uint64_t)hi32 << 32 | lo32;
+  }
+  // The place of the word of units j .. j+UPT-1, row r of a tile: step j / 32, lane group (j % 32) / 8.
+  static __device__ __forceinline__ int place(int j, int r) {
+    return (j / 32 * NA + j % 8 / UPT) * 64 + j % 32 / 8 * 16 + r;
+  }
+};
+
 template <bool BF16, int WK>  // WK: 32-k steps per wave, at most
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_enc_scan(ScanArgs a) {
-  constexpr int NPL = BF16 ? 1 : 2;         // planes of a weight fragment
-  constexpr int NA = BF16 ? 2 : 4;          // words per lane and step
-  constexpr int UPT = BF16 ? 4 : 2;         // units per word
-  typedef float fu __attribute__((ext_vector_type(UPT)));
+  using K = Scan<BF16>;
+  using fu = typename K::fu;
+  constexpr int NPL = K::NPL, NA = K::NA, UPT = K::UPT;
   __shared__ f32x4 red[2][8][3][2][64];     // [position parity][wave][gate][row tile][lane]
   const int ub = blockIdx.x, dir = blockIdx.y, grp = blockIdx.z;
   const int nub = gridDim.x, ngrp = gridDim.z;
@@ -120,16 +195,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   // this wave's weights: steps s0 .. s1 - 1
   const int s0 = wave < a.splits ? scan_first(BF16, nks, a.splits, wave) : nks;
   const int s1 = wave < a.splits ? scan_first(BF16, nks, a.splits, wave + 1) : nks;
-  f32x4 w[3][WK][NPL];
+  f32x4 w[WK][3][NPL];
 #pragma unroll
-  for (int i = 0; i < WK; ++i) {
-    const int s = s0 + i;
+  for (int i = 0; i < WK; ++i)
 #pragma unroll
     for (int g = 0; g < 3; ++g)
 #pragma unroll
-      for (int p = 0; p < NPL; ++p)
-        w[g][i][p] = s < s1 ? a.W[(((((int64_t)dir * nub + ub) * 3 + g) * nks + s) * NPL + p) * 64 + lane] : zero4();
-  }
+      for (int p = 0; p < NPL; ++p) w[i][g][p] = s0 + i < s1 ? K::weight(a, dir, nub, ub, g, s0 + i, p, lane) : zero4();
 
   // the cell: thread tid owns UPT units of one sentence
   const int tid = threadIdx.x, cl = tid & 63;
@@ -147,8 +219,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   const int64_t tile_words = (int64_t)nks * NA * 64;           // words of one row tile of a position
   const int64_t pos_words = 2 * (int64_t)ngrp * 2 * tile_words;  // words of a position
   uint64_t* const base = a.words + (dir * ngrp + grp) * 2 * tile_words;
-  // word of units j .. j+UPT-1 in the operand: step j / 32, lane group (j % 32) / 8
-  const int64_t my_word = crt * tile_words + ((int64_t)(j / 32) * NA + (j % 8) / UPT) * 64 + (j % 32) / 8 * 16 + (cl & 15);
+  const int64_t my_word = crt * tile_words + K::place(j, cl & 15);
   bool waiting = true;  // false once a wait has run out
 
   for (int t = 0; t < Tpad; ++t) {
@@ -163,9 +234,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     fu sr{}, sz{}, sn{};
     if (t > 0) {
       const uint64_t* src = base + (t - 1) * pos_words;
-      f32x4 acc[3][2];
-#pragma unroll
-      for (int g = 0; g < 3; ++g) acc[g][0] = acc[g][1] = zero4();
       static_for<2>([&](auto rtc) {
         constexpr int rt = decltype(rtc)::value;
         if (rt >= nrt) return;
@@ -197,9 +265,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
             for (int q = 0; q < NA; ++q) ok = ok && (off[i][q] < 0 || x[i][q] != kNotYet);
           if (__builtin_amdgcn_ballot_w64(!ok) == 0 || !waiting) break;
-          if (polls >= kScanPolls) {
+          if (polls >= a.polls) {
             waiting = false;
-            if (lane == 0) atomicOr(a.err, 2);
+            if (lane == 0) atomicOr(a.gave_up, 1);
           }
           // Half a microsecond between polls: the polls of 1,024 waves share
           // the path of the stores they wait for (sleeps of 64, 512, 1,024 and
@@ -207,33 +275,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
           // a source, 80 of 32 bf16 ones 513, 504, 496 and 504 us).
           __builtin_amdgcn_s_sleep(16);
         }
+        f32x4 acc[3] = {zero4(), zero4(), zero4()};
 #pragma unroll
         for (int i = 0; i < WK; ++i) {
 #pragma unroll
           for (int q = 0; q < NA; ++q) x[i][q] = off[i][q] < 0 ? 0 : x[i][q];
-          typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-          if constexpr (BF16) {
-            const u32x4 v = {(uint32_t)x[i][0], (uint32_t)(x[i][0] >> 32), (uint32_t)x[i][1], (uint32_t)(x[i][1] >> 32)};
-#pragma unroll
-            for (int g = 0; g < 3; ++g)
-              acc[g][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[g][i][0]),
-                                                                   __builtin_bit_cast(bf16x8, v), acc[g][rt], 0, 0, 0);
-          } else {
-            const u32x4 vh = {(uint32_t)x[i][0], (uint32_t)x[i][1], (uint32_t)x[i][2], (uint32_t)x[i][3]};
-            const u32x4 vl = {(uint32_t)(x[i][0] >> 32), (uint32_t)(x[i][1] >> 32), (uint32_t)(x[i][2] >> 32),
-                              (uint32_t)(x[i][3] >> 32)};
-            const f16x8 hh = __builtin_bit_cast(f16x8, vh), hl = __builtin_bit_cast(f16x8, vl);
-#pragma unroll
-            for (int g = 0; g < 3; ++g) {
-              f32x4& d = acc[g][rt];
-              d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[g][i][NPL - 1]), hh, d, 0, 0, 0);
-              d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[g][i][0]), hl, d, 0, 0, 0);
-              d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[g][i][0]), hh, d, 0, 0, 0);
-            }
-          }
+          K::step(w[i], x[i], acc);
         }
 #pragma unroll
-        for (int g = 0; g < 3; ++g) red[t & 1][wave][g][rt][lane] = acc[g][rt];
+        for (int g = 0; g < 3; ++g) red[t & 1][wave][g][rt][lane] = acc[g];
       });
       __syncthreads();
       if (cell) {
@@ -246,35 +296,79 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
       }
     }
     if (cell) {
-      fu o;
+      hp = K::cell(a, sr, sz, sn, br, bz, bni, bns, xr, xz, xn, hp, pos < L);
+      *(fu*)(a.ctx + ((int64_t)crow * Tpad + pos) * 2 * H + dir * H + j) = hp;
+      if (t + 1 < Tpad)
+        __hip_atomic_store(base + t * pos_words + my_word, K::word(a, hp), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
+// The same recurrence with no block waiting for another, after a launch of
+// k_enc_scan in which a wait ran out (else it ends at once): a block computes
+// every unit of 16 sentences of one direction, position after position, its
+// states in LDS in k_enc_scan's words and the weights read again from L2 for
+// every position (0.2 to 0.3 ms a position at H = 1,024), with the same sums in the same
+// order.
+template <bool BF16>
+__global__ __launch_bounds__(512) void k_enc_alone(ScanArgs a) {
+  using K = Scan<BF16>;
+  using fu = typename K::fu;
+  constexpr int NPL = K::NPL, NA = K::NA, UPT = K::UPT;
+  __shared__ uint64_t state[2][kScanMaxH / 32 * NA * 64];  // [position parity]
+  __shared__ f32x4 red[8][3][64];
+  if (*a.gave_up == 0) return;
+  const int row0 = blockIdx.x * 16, dir = blockIdx.y;
+  const int H = a.H, nks = a.nks, Tpad = a.Tpad, nub = (H + kScanUnits - 1) / kScanUnits;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int s0 = wave < a.splits ? scan_first(BF16, nks, a.splits, wave) : nks;
+  const int s1 = wave < a.splits ? scan_first(BF16, nks, a.splits, wave + 1) : nks;
+  const int tid = threadIdx.x, cl = tid & 63, part = BF16 ? 0 : (tid >> 6) & 1;
+  const int crow = row0 + (cl & 15), ju = 4 * (cl >> 4) + UPT * part;
+  const bool crow_ok = tid < 64 * (4 / UPT) && crow < a.S;
+  const int L = crow_ok ? a.len[crow] : 0;
+  for (int i = tid; i < nks * NA * 64; i += 512) state[0][i] = state[1][i] = 0;  // rows and units that do not exist
+  for (int t = 0; t < Tpad; ++t) {
+    const int pos = dir == 0 ? t : Tpad - 1 - t;
+    const uint64_t* prev = state[(t + 1) & 1];
+    for (int ub = 0; ub < nub; ++ub) {
+      __syncthreads();  // the last sums are read, the last position's states are there
+      if (t > 0) {
+        f32x4 acc[3] = {zero4(), zero4(), zero4()};
+        for (int s = s0; s < s1; ++s) {
+          f32x4 w[3][NPL];
+          uint64_t x[NA];
 #pragma unroll
-      for (int e = 0; e < UPT; ++e) {
-        const float inv = BF16 ? 1.f : a.inv;
-        const float hn = gru_cell(sr[e] * inv, sz[e] * inv, 0.f, sn[e] * inv, br[e], bz[e], bni[e], bns[e], xr[e], xz[e],
-                                  xn[e], hp[e]);
-        o[e] = pos < L ? hn : 0.f;
-      }
-      hp = o;
-      *(fu*)(a.ctx + ((int64_t)crow * Tpad + pos) * 2 * H + dir * H + j) = o;
-      if (t + 1 < Tpad) {
-        uint32_t lo32, hi32;
-        f32x2 c0, c1;
-        auto canon = [](float v) { return v == v ? v : __builtin_nanf(""); };
-        if constexpr (BF16) {
-          c0 = f32x2{canon(o[0]), canon(o[1])};
-          c1 = f32x2{canon(o[UPT - 2]), canon(o[UPT - 1])};
-          lo32 = __builtin_bit_cast(uint32_t, __builtin_convertvector(c0, bf16x2));
-          hi32 = __builtin_bit_cast(uint32_t, __builtin_convertvector(c1, bf16x2));
-        } else {
-          c0 = f32x2{canon(o[0]) * a.hscale, canon(o[1]) * a.hscale};
-          const f16x2 hi = __builtin_convertvector(c0, f16x2);
-          c1 = f32x2{c0[0] - (float)hi[0], c0[1] - (float)hi[1]};
-          lo32 = __builtin_bit_cast(uint32_t, hi);
-          hi32 = __builtin_bit_cast(uint32_t, __builtin_convertvector(c1, f16x2));
+          for (int g = 0; g < 3; ++g)
+#pragma unroll
+            for (int p = 0; p < NPL; ++p) w[g][p] = K::weight(a, dir, nub, ub, g, s, p, lane);
+#pragma unroll
+          for (int q = 0; q < NA; ++q) x[q] = prev[(s * NA + q) * 64 + lane];
+          K::step(w, x, acc);
         }
-        __hip_atomic_store(base + t * pos_words + my_word, (uint64_t)hi32 << 32 | lo32, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int g = 0; g < 3; ++g) red[wave][g][lane] = acc[g];
+        __syncthreads();
       }
+      const int j = ub * kScanUnits + ju;
+      if (!crow_ok || j >= H) continue;
+      fu sr{}, sz{}, sn{}, hp{};
+      float* out = a.ctx + ((int64_t)crow * Tpad + pos) * 2 * H + dir * H + j;
+      if (t > 0) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+          sr += *(const fu*)((const float*)&red[v][0][cl] + UPT * part);
+          sz += *(const fu*)((const float*)&red[v][1][cl] + UPT * part);
+          sn += *(const fu*)((const float*)&red[v][2][cl] + UPT * part);
+        }
+        hp = *(const fu*)(out + (dir == 0 ? -2 * H : 2 * H));  // this thread's own store of the last position
+      }
+      const float* x = a.xp + ((int64_t)crow * Tpad + pos) * 6 * H + dir * 3 * H + j;
+      const fu o = K::cell(a, sr, sz, sn, *(const fu*)(a.brz + j), *(const fu*)(a.brz + H + j), *(const fu*)(a.bni + j),
+                           *(const fu*)(a.bns + j), *(const fu*)x, *(const fu*)(x + H), *(const fu*)(x + 2 * H), hp,
+                           pos < L);
+      *(fu*)out = o;
+      state[t & 1][K::place(j, cl & 15)] = K::word(a, o);
     }
   }
 }
@@ -302,7 +396,8 @@ static int scan_groups(int H, int cus) { return std::min(2, cus / (2 * scan_bloc
 
 // Waves that share K, and the steps that the longest run of one has.  fp32 weights take twice the registers, so four
 // steps a wave (H of at most 1,024) against eight.
-constexpr int kScanMaxH = 1024, kScanLongF32 = 4, kScanLongBF16 = 8;
+constexpr int kScanLongF32 = 4, kScanLongBF16 = 8;
+static_assert(kScanMaxH == 32 * 8 * kScanLongF32, "eight waves' runs hold K");
 static int scan_splits(bool bf16, int chain_ks) { return bf16 ? chain_ks : 8; }
 static int scan_longest(int H, bool bf16, int splits) {
   int n = 0;
@@ -320,8 +415,8 @@ size_t scan_words_bytes(int S, int Tpad, int H, bool bf16, int chain_ks, int cus
   return n > ((size_t)128 << 20) ? 0 : n;
 }
 
-hipError_t launch_enc_scan(const void* W, const float* xp, float* ctx, const int32_t* len, void* words, int* err,
-                           const GruEpi& bias, int S, int Tpad, int H, bool bf16, int chain_ks, int scale, int cus,
+hipError_t launch_enc_scan(const void* W, const float* xp, float* ctx, const int32_t* len, void* words, int* gave_up,
+                           int form, const GruEpi& bias, int S, int Tpad, int H, bool bf16, int chain_ks, int scale, int cus,
                            hipStream_t st) {
   const int g = scan_groups(H, cus), per = std::min(g, ceil_div(S, kScanRows)) * kScanRows;
   const int64_t bytes = (int64_t)scan_words_bytes(S, Tpad, H, bf16, chain_ks, cus);
@@ -331,14 +426,16 @@ hipError_t launch_enc_scan(const void* W, const float* xp, float* ctx, const int
                              : (scan_longest(H, bf16, splits) <= 4 ? (const void*)k_enc_scan<true, 4>
                                                                    : (const void*)k_enc_scan<true, kScanLongBF16>);
   for (int s0 = 0; s0 < S; s0 += per) {
-    hipLaunchKernelGGL(k_fill_words, dim3(ceil_div(bytes / 16, 256)), dim3(256), 0, st, (uint64_t*)words, bytes / 16);
+    hipLaunchKernelGGL(k_fill_words, dim3(ceil_div(bytes / 16, 256)), dim3(256), 0, st, (uint64_t*)words, bytes / 16,
+                       gave_up);
     ScanArgs a{};
     a.W = (const f32x4*)W;
     a.xp = xp + (int64_t)s0 * Tpad * 6 * H;
     a.ctx = ctx + (int64_t)s0 * Tpad * 2 * H;
     a.len = len + s0;
     a.words = (uint64_t*)words;
-    a.err = err;
+    a.gave_up = gave_up;
+    a.polls = form == 2 ? 0 : kScanPolls;
     a.brz = bias.brz;
     a.bni = bias.bni;
     a.bns = bias.bns;
@@ -353,6 +450,11 @@ hipError_t launch_enc_scan(const void* W, const float* xp, float* ctx, const int
     const dim3 grid(scan_blocks(H), 2, ceil_div(a.S, kScanRows));
     const hipError_t e = hipLaunchCooperativeKernel(kernel, grid, dim3(512), args, 0, st);
     if (e != hipSuccess) return e;
+    const dim3 rest(ceil_div(a.S, 16), 2);
+    if (bf16)
+      hipLaunchKernelGGL(k_enc_alone<true>, rest, dim3(512), 0, st, a);
+    else
+      hipLaunchKernelGGL(k_enc_alone<false>, rest, dim3(512), 0, st, a);
   }
   return hipGetLastError();
 }

@@ -328,12 +328,13 @@ hipError_t launch_vocab_sp(const float* t, int M, int E, const SplitW& W, int V,
 // GRU tile; scale: fp32 models' exponent, split_scale), the scratch words of
 // a source (0: the launch does not take it), and the launch itself.
 // chain_ks: the K splits of the chain of launches, whose order of sums a
-// bf16 model's states have in either form.
+// bf16 model's states have in either form.  gave_up: a flag of the source's.
+// form 2: no wait is waited out (a test's).
 size_t scan_weight_bytes(int H, bool bf16);
 hipError_t launch_scan_pack(const Packed (&U)[2], int H, bool bf16, int hb, int scale, void* out, hipStream_t st);
 size_t scan_words_bytes(int S, int Tpad, int H, bool bf16, int chain_ks, int cus);
-hipError_t launch_enc_scan(const void* W, const float* xp, float* ctx, const int32_t* len, void* words, int* err,
-                           const GruEpi& bias, int S, int Tpad, int H, bool bf16, int chain_ks, int scale, int cus,
+hipError_t launch_enc_scan(const void* W, const float* xp, float* ctx, const int32_t* len, void* words, int* gave_up,
+                           int form, const GruEpi& bias, int S, int Tpad, int H, bool bf16, int chain_ks, int scale, int cus,
                            hipStream_t st);
 
 // The step up to the readout of a small fp32 model in one kernel

@@ -80,6 +80,32 @@ def test_bf16_states_are_the_chains_bit_for_bit(kw):
     g.close()
 
 
+@pytest.mark.parametrize("wtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kw", [dict(), dict(S=17, H=100), dict(S=33, H=260), dict(S=70, H=1024), dict(S=5, H=4, E=4, A=4),
+                                dict(S=3, Tpad=1, len_hi=1), dict(S=20, H=960, Tpad=12, len_hi=12)],
+                         ids=lambda kw: "_".join(f"{k}{v}" for k, v in kw.items()) or "one")
+def test_a_wait_that_runs_out_changes_nothing(kw, wtype):
+    """With no wait waited out, the kernel that needs no other block computes
+    the states the one launch gives, and the call is not an error."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_cases
+    from paper_1605_04809_amd import binding as nb
+    wl = unit_gain(BASE.replace(wtype=wtype, **kw))
+    g = gpu_cases.GpuRun(wl)
+    prev = nb.debug_encode_form(2)
+    try:
+        c = gpu_cases.GpuRun(wl, model=g.model)
+    finally:
+        nb.debug_encode_form(prev)
+    for a, b in zip([*g.src.copy_out(), g.s0], [*c.src.copy_out(), c.s0]):
+        np.testing.assert_array_equal(a.cpu().numpy().view(np.int32), b.cpu().numpy().view(np.int32))
+    assert nb.nmt_stream_status(g.model) == nb.NMT_OK
+    c.src.close()
+    g.close()
+
+
 def test_sources_on_two_streams_at_once():
     """Two recurrences in flight together give what each gives alone."""
     torch = pytest.importorskip("torch")
