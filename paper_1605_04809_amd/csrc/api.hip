@@ -404,7 +404,7 @@ hipError_t word_tables(nmt_model* m, hipStream_t st) {
   const AOperand A = make_a(V, {emb_seg(m, m->emb_tgt, nullptr, V)});
   auto table = [&](const Packed& W, float* out, int N) {
     const PlainEpi ep{out, N, nullptr, N, 0, nullptr, 1};
-    return m->split ? launch_plain_sp(SpA{(const float*)m->emb_tgt, nullptr, 0, E, E, V, m->emb_scale_tgt, 0.f}, W.sp,
+    return m->split ? launch_plain_sp(SpA{(const float*)m->emb_tgt, nullptr, 0, E, E, V, m->emb_scale_tgt, 0.f, 0.f}, W.sp,
                                       ep, m->cus, st)
                     : launch_gemm_plain(Tile::Large, A, W, ep, st);
   };
@@ -469,6 +469,9 @@ hipError_t split_weights(nmt_model* m, hipStream_t st) {
     sp.steps = split_steps(it.K, vocab);
     sp.blocks = it.gru_hb ? 3 * (int64_t)ceil_div(d.H, 32) : it.W->Npad / 32;
     sp.scale = split_scale(r);
+    sp.w32 = (const float*)it.W->d;
+    sp.n32 = it.W->Npad;
+    sp.gru_hb = it.gru_hb;
     return sp.scale != kNoSplit &&
            (vocab ? split_vocab_fits(it.K, sp.blocks) : split_bytes(sp.blocks, sp.steps) < ((int64_t)1 << 31));
   };
@@ -746,7 +749,7 @@ hipError_t source_keys(nmt_model* m, nmt_source* src, hipStream_t st) {
   const int C = 2 * d.H;
   AOperand A = make_a(src->S * src->Tpad, {make_seg(src->ctx, C, C, 0, m->kc)});
   PlainEpi ep{src->pctx, d.A, m->att_b, d.A, 0, src->len, src->Tpad};
-  const SpA As{src->ctx, nullptr, 0, C, C, src->S * src->Tpad, kSplitState, 0.f};
+  const SpA As{src->ctx, nullptr, 0, C, C, src->S * src->Tpad, kSplitState, 0.f, 0.f};
   hipError_t e = m->split ? launch_plain_sp(As, m->att_Wc.sp, ep, m->cus, st)
                           : launch_gemm_plain(Tile::Large, A, m->att_Wc, ep, st);
   if (e == hipSuccess) e = launch_key_factors(src->S, src->Tpad, d.A, src->pctx, src->kfac, src->kbig, st);
@@ -1020,7 +1023,7 @@ nmt_status nmt_encode(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* d_sr
     AOperand A = make_a((int)rows, {emb_seg(m, m->emb_src, d_src_ids, d.V_src)});
     PlainEpi ep{Xp, 6 * H, m->enc_in_b, 6 * H, 0, nullptr, 1};
     e = m->split ? launch_plain_sp(SpA{(const float*)m->emb_src, d_src_ids, d.V_src, E, E, (int)rows, m->emb_scale_src,
-                                       0.f},
+                                       0.f, 0.f},
                                    m->enc_in.sp, ep, m->cus, st)
                  : launch_gemm_plain(Tile::Large, A, m->enc_in, ep, st);
   }
@@ -1068,7 +1071,7 @@ nmt_status nmt_encode(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* d_sr
       for (int dir = 0; dir < 2; ++dir) {
         ep[dir] = p[dir].ep;
         w[dir] = &m->enc_U[dir].sp;
-        a[dir] = SpA{ep[dir].h, nullptr, 0, ldc, ep[dir].h ? H : 0, S, kSplitState, 0.f};
+        a[dir] = SpA{ep[dir].h, nullptr, 0, ldc, ep[dir].h ? H : 0, S, kSplitState, 0.f, 0.f};
       }
       e = launch_gru_sp(a, w, ep, 2, m->cus, st);
       continue;
@@ -1084,7 +1087,7 @@ nmt_status nmt_encode(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* d_sr
     if (e == hipSuccess) {
       AOperand A = make_a(S, {make_seg(mean, C, C, 0, m->kc)});
       PlainEpi ep{d_s0_out, H, m->init_b, H, 1, nullptr, 1};
-      e = m->split ? launch_plain_sp(SpA{mean, nullptr, 0, C, C, S, kSplitState, 0.f}, m->init_W.sp, ep, m->cus, st)
+      e = m->split ? launch_plain_sp(SpA{mean, nullptr, 0, C, C, S, kSplitState, 0.f, 0.f}, m->init_W.sp, ep, m->cus, st)
                    : launch_gemm_plain(Tile::Small, A, m->init_W, ep, st);
     }
   }
@@ -1268,7 +1271,7 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
   auto run_gru = [&](const GruProblem& g, const SplitW& sp, int ks) {
     if (m->split) {  // one segment: the state rows
       const ASeg& sg = g.A.seg[0];
-      const SpA a{(const float*)sg.p, sg.gather, sg.gmax, sg.ld, sg.K, B, kSplitState, 0.f};
+      const SpA a{(const float*)sg.p, sg.gather, sg.gmax, sg.ld, sg.K, B, kSplitState, 0.f, 0.f};
       const SplitW* w = &sp;
       return launch_gru_sp(&a, &w, &g.ep, 1, m->cus, st);
     }
@@ -1287,7 +1290,7 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
     // a split query leaves its sums for the attention to add as it loads
     // them (the test switch's forced streaming writes q itself)
     ep.defer_reduce = L.ks_q > 1 && !gemm_stream_forced(g_gemm_form.load(std::memory_order_relaxed));
-    e = m->split ? launch_plain_sp(SpA{s1, nullptr, 0, H, H, B, kSplitState, 0.f}, m->att_Wq.sp, ep, m->cus, st)
+    e = m->split ? launch_plain_sp(SpA{s1, nullptr, 0, H, H, B, kSplitState, 0.f, 0.f}, m->att_Wq.sp, ep, m->cus, st)
                  : launch_gemm_plain(Tile::Small, make_a(B, {state_seg(s1, s1h, 0)}), m->att_Wq, ep, st, m->cus);
     qsrc = ep.defer_reduce ? QuerySrc{ep.part, L.ks_q, (int64_t)B * Aw} : QuerySrc{q, 1, 0};
   }
@@ -1345,7 +1348,7 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
       ep.ldo = bf16_row(E);
     }
     if (m->split)
-      e = launch_plain_sp(SpA{d_s_new, nullptr, 0, H, H, B, kSplitState, 0.f}, m->ro.sp, ep, m->cus, st);
+      e = launch_plain_sp(SpA{d_s_new, nullptr, 0, H, H, B, kSplitState, 0.f, 0.f}, m->ro.sp, ep, m->cus, st);
     else
       e = launch_gemm_plain(Tile::Small,
                           m->precomp ? make_a(B, {make_seg(d_s_new, H, H, 0, m->kc)})

@@ -66,6 +66,10 @@ struct SplitW {
   int64_t blocks = 0;     // 32-column blocks (GRU: r, z, candidate of 32 units each)
   int K = 0, steps = 0;   // rows of the matrix, and 16-k steps they are padded to
   int scale = 0;
+  // the fp32 matrix [Kpad/4][n32][4], its columns in GRU tiles of gru_hb units (0: plain)
+  const float* w32 = nullptr;
+  int64_t n32 = 0;
+  int gru_hb = 0;
 };
 
 // A weight matrix packed for one kernel family: [Kpad/KV][Npad][KV] of fp32
@@ -280,10 +284,13 @@ struct SpA {
   int64_t ld;
   int32_t K, M;
   int32_t scale;
-  float limit;  // magnitude from which a row is computed by the fp32 MFMA (set by the launchers)
+  // rows whose largest magnitude is at least most, or below least but not
+  // zero, are computed by the fp32 MFMA (set by the launchers)
+  float most, least;
 };
 constexpr int kSplitReadout = 14;  // activations' scale: tanh readouts (at most 1)
-constexpr int kSplitState = 12;    // states and annotations (at most 1 from the model; up to 16 stay on the halves)
+// states and annotations (at most 1 from the model; a row whose largest is in [2^-12, 16) stays on the halves)
+constexpr int kSplitState = 12;
 constexpr int kSpLongK = 256;      // K from which the tile GEMM splits K between wave groups
 constexpr int kSpShortChunk = 4, kSpLongChunk = 16;  // steps a shorter (longer) K is padded to multiples of
 constexpr int kNoSplit = 1 << 20;

@@ -20,10 +20,15 @@
 // most 2^-39 of its matrix's largest element, below fp32's own rounding of
 // any column whose largest element is within 2^-14 of the matrix's; models
 // with other weights (and non-finite ones) keep the fp32 MFMA kernels
-// (split_scale, checked when the model is made).  Activations beyond the
-// range (a caller's states or annotations can hold any fp32 value) are found
-// while they are staged, and their rows are computed again with the fp32
-// MFMA (k_gemm_sp's wide rows).
+// (split_scale, checked when the model is made).  A row of activations the
+// halves would hold less precisely than fp32 (a caller's states or
+// annotations can hold any fp32 value) is found while it is staged, and
+// computed again with the fp32 MFMA (k_gemm_sp's rows outside the range).
+// Readouts and the encoder's states need no such check: they come out of
+// tanhf_ or a cell with an absolute error of a few 2^-24, next to which the
+// halves' 2^-39 and 2^-37 do not count.  The splitting of an operand into
+// the parts a narrower format holds is Dekker's (1971); on matrix units see
+// Markidis et al. (2018) and Ootomo and Yokota (2022).
 //
 // Weights are packed by the wave: [32-column block][16-k step][hi, lo]
 // [k half][column][8 halves], so a wave's fragment is one contiguous 1 KB
@@ -282,17 +287,21 @@ hipError_t launch_scaled_bias(const Packed& W, int scale, int64_t n, float* out,
 // kSpLongK takes one k group and short chunks, whose sums do not depend on
 // the tile.
 //
-// Wide rows.  A row with an element at or beyond the halves' range (or an
-// infinity) is computed again by the fp32 MFMA from the fp32 row and the
-// halves' sums, and only that row's values are replaced, so a row's results
-// never depend on its neighbours.  NaN needs no such path: it fills its
-// row's products either way.
+// Rows outside the range.  A row with an element at or beyond the halves'
+// range (or an infinity), and one whose largest element is below the least
+// that they hold to 2^-25 of it, is computed again by the fp32 MFMA from the
+// fp32 row and the fp32 weights, and only that row's values are replaced, so
+// a row's results never depend on its neighbours.  NaN needs no such path: it
+// fills its row's products either way.
 struct SpProblem {
   SpA A;
   const char* W;
   int64_t wbytes;
   int32_t steps, blocks;
-  float ascale, inv, winv;
+  const f32x4* w32;
+  int64_t n32;
+  int32_t hb;
+  float ascale, inv;
   GruEpi g;
   PlainEpi p;
 };
@@ -320,6 +329,22 @@ __device__ __forceinline__ f32x4 load4_or0(const float* base, int64_t off, bool 
   return f32x4{ok ? v[0] : 0.f, ok ? v[1] : 0.f, ok ? v[2] : 0.f, ok ? v[3] : 0.f};
 }
 
+// The largest of N consecutive lanes' values, in all of them.
+template <int N>
+__device__ __forceinline__ float lanes_max(float v) {
+  static_assert(N == 8 || N == 16 || N == 32, "lanes of a row");
+  auto with = [&](auto ctrl) {
+    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf,
+                                                                    0xf, true)));
+  };
+  with(std::integral_constant<int, 0xB1>{});              // lane ^ 1
+  with(std::integral_constant<int, 0x4E>{});              // lane ^ 2
+  with(std::integral_constant<int, 0x141>{});             // 7 - lane of 8
+  if constexpr (N >= 16) with(std::integral_constant<int, 0x140>{});  // 15 - lane of 16
+  if constexpr (N >= 32) v = fmaxf(v, __shfl_xor(v, 16, 64));
+  return v;
+}
+
 template <int RF, int CF, int WM, int WN, int KS, int CH>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_sp(SpBatch batch, int nrow,
                                                                                         int ntile) {
@@ -331,7 +356,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   constexpr bool GRU = CF == 3;
   static_assert(NA >= 1 && TM * VPC % NT == 0 && NKL % VPF == 0, "whole vectors, ring slots fixed within a chunk");
   __shared__ f32x4 As[2 * 2 * VPC * TM];  // [stage][vector][hi, lo][row ^ vector]
-  __shared__ int wide[TM], any_wide;
+  __shared__ float row_max[TM];
   constexpr int STG = 2 * VPC * TM;
   const SpProblem& Pb = batch.p[blockIdx.y];
   const SpA A = Pb.A;
@@ -444,10 +469,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   for (int i = 0; i < RF; ++i)
 #pragma unroll
     for (int f = 0; f < CF; ++f) acc[i][f] = f32x16{};
-  for (int i = threadIdx.x; i < TM; i += NT) wide[i] = 0;
-  if (threadIdx.x == 0) any_wide = 0;
 
-  if (nch > 0) {  // (without a product the flags below are never set)
+  if (nch > 0) {  // (without a product every row's largest is 0: in range)
     f32x4 ring[VPF][CF][2];
 #pragma unroll
     for (int p = 0; p < VPF; ++p) wload(ring[p], p / NKL, p % NKL);
@@ -577,41 +600,44 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
         sum[t][f] = f32x4{acc[i][f][4 * q], acc[i][f][4 * q + 1], acc[i][f][4 * q + 2], acc[i][f][4 * q + 3]};
       }
   }
-  // (an LDS flag and a plain barrier: __syncthreads_or reads the block size
-  // from the dispatch packet, in host memory, which cost each launch 10 us)
 #pragma unroll
-  for (int i = 0; i < NA; ++i)
-    if (amax[i] >= A.limit) {
-      wide[arow + RP * i] = 1;
-      any_wide = 1;
-    }
+  for (int i = 0; i < NA; ++i) {
+    const float mx = lanes_max<VPC>(amax[i]);
+    if (sv == 0) row_max[arow + RP * i] = mx;
+  }
   __syncthreads();
   if (!busy) return;
 #pragma unroll
   for (int t = 0; t < NPK; ++t)
 #pragma unroll
     for (int f = 0; f < CF; ++f) sum[t][f] *= Pb.inv;
-  if (any_wide) {
+  // rows outside the halves' range: a wave's pieces are of one row fragment, or (KS = 1) of every one
+  constexpr int NI = KS == 1 ? RF : 1, TI = NPK / NI;
 #pragma unroll
-    for (int t = 0; t < NPK; ++t) {
-      const int i = piece_i(t), q = piece_q(t), lrow = r0 + 32 * i + l32, ro = row_off(m0 + lrow);
-      const bool mine = wide[lrow] != 0;
-      for (int f = 0; f < CF; ++f) {
-        f32x16 s = f32x16{};
-        for (int k8 = 0; k8 < 2 * steps; ++k8) {  // 8 k at a time; lane half h holds k 4 h .. 4 h + 3 of them
-          const int k = 8 * k8 + 4 * h;
-          const f32x4 x = buf_load(ares, k < A.K ? ro + k * 4 : kNoLoad, 0);
-          // halves 4 h .. of vector (step k8 / 2, half k8 % 2), column l32
-          const int o = (k8 >> 1) * 2048 + (k8 & 1) * 512 + l32 * 16 + h * 8;
-          f16x4 wh{}, wl{};
-          if (cb0 + f < Pb.blocks) {
-            wh = *(const f16x4*)(Pb.W + (int64_t)(cb0 + f) * steps * 2048 + o);
-            wl = *(const f16x4*)(Pb.W + (int64_t)(cb0 + f) * steps * 2048 + o + 1024);
-          }
+  for (int ii = 0; ii < NI; ++ii) {
+    const int i = piece_i(TI * ii), lrow = r0 + 32 * i + l32;
+    const float mx = row_max[lrow];
+    const bool mine = mx >= A.most || (mx > 0.f && mx < A.least);
+    if (__builtin_amdgcn_ballot_w64(mine) == 0) continue;
+    const int ro = row_off(m0 + lrow);
+    for (int f = 0; f < CF; ++f) {
+      const int b = cb0 + f;
+      if (b >= Pb.blocks) continue;
+      int64_t n = (int64_t)b * 32 + l32;
+      if constexpr (GRU) {
+        const int u = b / 3 * 32;
+        n = (int64_t)(u / Pb.hb) * 3 * Pb.hb + (b % 3) * Pb.hb + u % Pb.hb + l32;
+      }
+      f32x16 s = f32x16{};
+      for (int k = 0; k < A.K; k += 8) {  // lane half h holds k 4 h .. 4 h + 3 of eight
+        const f32x4 x = buf_load(ares, k + 4 * h < A.K ? ro + (k + 4 * h) * 4 : kNoLoad, 0);
+        const f32x4 w = Pb.w32[(int64_t)(k / 4 + h) * Pb.n32 + n];
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(((float)wh[e] + (float)wl[e]) * Pb.winv, x[e], s, 0, 0, 0);
-        }
+        for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(w[e], x[e], s, 0, 0, 0);
+      }
+#pragma unroll
+      for (int t = TI * ii; t < TI * (ii + 1); ++t) {
+        const int q = piece_q(t);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float v = q == 0 ? s[e] : (q == 1 ? s[4 + e] : (q == 2 ? s[8 + e] : s[12 + e]));
@@ -681,11 +707,14 @@ static bool sp_problem(SpProblem& P, const SpA& A, const SplitW& W) {
   P.wbytes = split_bytes(W.blocks, W.steps);
   P.steps = W.steps;
   P.blocks = (int)W.blocks;
-  P.A.limit = std::ldexp(65504.f, -A.scale);
+  P.A.most = std::ldexp(65504.f, -A.scale);
+  P.A.least = std::ldexp(1.f, -A.scale);
+  P.w32 = (const f32x4*)W.w32;
+  P.n32 = W.n32;
+  P.hb = W.gru_hb;
   P.ascale = std::ldexp(1.f, A.scale);
   P.inv = std::ldexp(1.f, -(A.scale + W.scale));
-  P.winv = std::ldexp(1.f, -W.scale);
-  if (!W.d || P.wbytes >= ((int64_t)1 << 31) || A.K % 4 || A.ld % 4) return false;
+  if (!W.d || !W.w32 || P.wbytes >= ((int64_t)1 << 31) || A.K % 4 || A.ld % 4) return false;
   if (A.K <= 0) return true;  // no product: the epilogue alone
   return A.p && (!A.gather || A.gmax >= 1) && W.steps * 16 >= A.K && W.steps == split_steps(W.K, false) &&
          (int64_t)(A.gather ? A.gmax : A.M) * A.ld * 4 < ((int64_t)1 << 31);

@@ -100,6 +100,61 @@ def test_states_beyond_the_halves_range(gpu, B):
     g32.close()
 
 
+# A GRU tile of each form at H = 1,024 on 256 CUs: 32, 64 and 128 rows, eight, four, two and one k groups.
+@pytest.mark.parametrize("B", [33, 300, 700, 2000, 4000])
+def test_states_outside_the_halves_range_in_every_tile(gpu, B):
+    """Rows beyond the range and rows far below it match the oracle in every
+    GRU tile, and the rows beside them do not change by a bit."""
+    wl = unit_gain(BASE.replace(B=B, H=1024, A=64, E=36, V=64))
+    wl.params["g1_U"] *= np.float32(2.0 ** 24)   # states of 2^-24 carry the first GRU
+    s = (wl.s_prev * np.float32(2.0 ** -24)).astype(np.float32)
+    plain = s.copy()
+    wide = np.array([1, 31, B // 2, B - 1])
+    s[wide] = wl.s_prev[wide] * 2.0 ** -24
+    s[wide, [0, 511, 700, 1023]] = [900.0, -16.0, 7e4, 20.0]
+    zero = np.array([5, B - 3])
+    s[zero] = plain[zero] = 0.0
+    g, o = gpu.GpuRun(wl), gpu.OracleRun(wl)
+    rest = (wl.y_prev, wl.sent_id, wl.req)
+    got, base, ref = g.step(s, *rest), g.step(plain, *rest), o.step(plain, *rest)
+    same = np.setdiff1d(np.arange(B), wide)
+    for k in ("logp", "logZ", "s_new", "s1", "t"):
+        np.testing.assert_array_equal(got[k][same], base[k][same], err_msg=k)
+    check(gpu, base, ref, "far below the range")
+    # beyond it: one element of 16 and more times 2^24 saturates the gates, so s1 is 0 or 1 times the state, or +-1
+    wref = o.step(s, *rest)
+    d = np.abs(got["s1"][wide] - wref["s1"][wide]) / np.maximum(1.0, np.abs(wref["s1"][wide]))
+    assert np.mean(d > TOL_INTER) <= 1e-3, np.sort(d.ravel())[-8:]   # (a gate whose sum falls within rounding of 0)
+    g.close()
+
+
+# The plain product's tiles by their number of rows (keys of 1,024 columns on 256 CUs): 32 to 128 rows, one to eight
+# k groups, one and two column blocks a wave.
+@pytest.mark.parametrize("S,Tpad", [(2, 9), (8, 66), (10, 115), (20, 115), (40, 115), (50, 180)])
+def test_annotations_outside_the_halves_range_in_every_tile(gpu, S, Tpad):
+    """Keys of annotations of about 2^-24, some rows with an element of 16 to 3e4; errors relative to a row's largest products."""
+    from paper_1605_04809_amd import binding as nb
+    import oracle
+    wl = unit_gain(BASE.replace(S=S, Tpad=Tpad, len_hi=Tpad, A=1024, B=8))
+    wl.src_len[:] = Tpad
+    wl.params["att_Wc"] *= np.float32(2.0 ** 24)
+    wl.params["att_b"][:] = 0
+    ctx = (random_annotations(wl.cfg, seed=84) * np.float32(2.0 ** -24)).astype(np.float32)
+    big = [(0, 0, 5), (S - 1, Tpad - 1, 300), (S // 2, Tpad // 2, 511), (S - 1, 1, 0)]
+    for (a, b, c), v in zip(big, (40.0, -3e4, 16.0, 1e3)):
+        ctx[a, b, c] = v
+    m = nb.Model.from_workload(wl)
+    src = nb.nmt_source_from_annotations(m, gpu.cuda(ctx), wl.src_len)
+    keys = src.copy_out()[1].cpu().numpy()
+    _, ref = oracle.keys_from_annotations(oracle.Model.from_workload(wl), ctx, wl.src_len)
+    size = np.maximum(1.0, np.abs(ctx).max(-1, keepdims=True) * 2.0 ** 24)   # a row's products are about this large
+    err = np.abs(keys - ref) / size
+    print(S * Tpad, "rows:", f"{err.max():.1e}", flush=True)
+    assert err.max() <= TOL_INTER
+    src.close()
+    m.close()
+
+
 @pytest.mark.parametrize("what", ["tiny_column", "inf_weight", "masked_words", "lowest_bias"])
 def test_weights_outside_the_rule(gpu, what):
     """Weights the halves would hold less precisely (a column 2^-20 of the
