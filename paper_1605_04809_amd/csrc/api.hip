@@ -580,13 +580,25 @@ WsLayout ws_layout(const nmt_model* m, int64_t B) {
   off += al((size_t)B * d.E * 4);
   L.vtm = vocab_tm((int)B, d.V, m->bf16, m->out.Kpad, d.E, m->out.nbias, m->cus);
   L.nS = vocab_slices((int)B, d.V, m->bf16, m->cus, L.vtm);
-  int part_slices = L.nS;
-  if (m->out.sp.d) {
-    split_vocab_shape((int)B, d.V, m->cus, &L.vtm, &L.nS);
-    part_slices = std::max(part_slices, L.nS);
-  }
   L.part = off;
-  off += al((size_t)B * part_slices * sizeof(float2));
+  size_t part = al((size_t)B * L.nS * sizeof(float2));
+  if (!m->bf16) {
+    // The vocabulary kernel on the halves may take more slices.  Their
+    // partials then lie over the mixed projections and the query, dead by
+    // then; where those are too small, the region grows, whether this model's
+    // output weights are split or not.
+    int tm, nS;
+    split_vocab_shape((int)B, d.V, m->cus, &tm, &nS);
+    const size_t need = al((size_t)B * nS * sizeof(float2));
+    const bool over = need > part && m->precomp && need <= L.t - L.c;
+    if (need > part && !over) part = need;
+    if (m->out.sp.d) {
+      L.vtm = tm;
+      L.nS = nS;
+      if (over) L.part = L.c;
+    }
+  }
+  off += part;
   // The query GEMM splits its K where its tiles fit in one round of the CUs
   // (a forest's levels, the phrase loop, B = 1000 at A = 1024), the attention
   // adding the split sums as it loads the query: ruen_b1000 query 27.1 ->
@@ -625,7 +637,7 @@ WsLayout ws_layout(const nmt_model* m, int64_t B) {
   }
   L.total = off;
   // Split weights share K between the waves of a tile and use no partial
-  // sums; the bytes stay those of the fp32 MFMA form, so that a workspace
+  // sums; the bytes are those of the fp32 MFMA form, so that a workspace
   // serves every model of these sizes whichever form its weights allow (an
   // average can come out in another form than its members).
   if (m->split) L.ks_q = L.ks_ro = L.ks_g1 = L.ks_g2 = 1;

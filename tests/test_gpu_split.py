@@ -212,6 +212,27 @@ def test_the_scale_sees_every_row(gpu, kw, row):
     g.close()
 
 
+# Batches whose vocabulary takes more slices on the halves than on the fp32 MFMA (256 CUs): their partials over the
+# projections and the query, and (widths of 4) in a region of their own.
+@pytest.mark.parametrize("kw", [dict(B=558, V=13488), dict(B=2275, V=26024), dict(B=40, V=13488, H=4, A=4, E=4),
+                                dict(B=70, V=5000, H=256, A=132)],
+                         ids=lambda kw: "_".join(f"{k}{v}" for k, v in kw.items()))
+def test_a_workspace_serves_both_forms(gpu, kw):
+    import torch
+    from paper_1605_04809_amd import binding as nb
+    wl = unit_gain(BASE.replace(**{**dict(H=64, A=64, E=36), **kw}))
+    other = unit_gain(BASE.replace(**{**dict(H=64, A=64, E=36), **kw}))
+    other.params["out_W"][:, 3] *= np.float32(2.0 ** -20)   # not split
+    g, u = gpu.GpuRun(wl), gpu.GpuRun(other)
+    n = nb.nmt_score_workspace_bytes(u.model, wl.cfg.B)
+    assert n == nb.nmt_score_workspace_bytes(g.model, wl.cfg.B)
+    args = (wl.s_prev, wl.y_prev, wl.sent_id, wl.req)
+    for run, w in ((g, wl), (u, other)):
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+        check(gpu, run.step(*args, workspace=ws), gpu.OracleRun(w).step(*args), str(kw))
+        run.close()
+
+
 def test_average_takes_the_form_its_weights_allow(gpu):
     """Members in two forms average; the result equals the same weights loaded."""
     from paper_1605_04809_amd import binding as nb
