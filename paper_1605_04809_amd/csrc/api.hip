@@ -1238,8 +1238,13 @@ nmt_status score_step(nmt_model* m, const nmt_source* src, int32_t B, const floa
   };
   mark(0);
 
-  // small models: everything up to the readout in one kernel
-  const int small_R = m->precomp && !m->split && g_small_step.load(std::memory_order_relaxed)
+  // small models: everything up to the readout in one kernel, whose blocks
+  // write their rows' new states while others still read theirs: states in
+  // place (row for row), or apart from the pool
+  const uintptr_t new_lo = (uintptr_t)d_s_new, pool_lo = (uintptr_t)pool;
+  const bool in_place = !state_row && d_s_new == pool;
+  const bool apart = new_lo + (uintptr_t)B * H * 4 <= pool_lo || pool_lo + (uintptr_t)pool_rows * H * 4 <= new_lo;
+  const int small_R = m->precomp && !m->split && (in_place || apart) && g_small_step.load(std::memory_order_relaxed)
                           ? small_step_rows(B, H, Aw, E, src->Tpad, m->cus)
                           : 0;
   if (small_R > 0) {

@@ -129,7 +129,7 @@ nmt_status nmt_score_forest(nmt_model* m, const nmt_source* src, const nmt_fores
   for (int d = 1; d <= f->depth; ++d) {
     const int32_t r0 = f->row_base[d - 1], q0 = f->req_base[d - 1];
     const float* pool = d == 1 ? d_hyp_states : states;
-    const int32_t pool_rows = d == 1 ? f->n_hyp : f->n_rows;
+    const int32_t pool_rows = d == 1 ? f->n_hyp : r0;  // the levels before this one
     nmt_status rc = nmt_internal_score_step(m, src, f->rows_lv[d - 1], pool, pool_rows, d_state_row + r0, d_y + r0,
                                             d_sent + r0, d_off + f->off_base[d - 1], d_req + q0, f->req_lv[d - 1],
                                             logp + q0, states + (int64_t)r0 * H, ws + L.step, ws_bytes - L.step, st,

@@ -54,6 +54,28 @@ def test_one_kernel_equals_the_separate_ones(gpu, kw):
     g.close()
 
 
+@pytest.mark.parametrize("shift", [1, 37, -1, -37])
+@pytest.mark.parametrize("B", [300, 2000])
+def test_new_states_over_a_part_of_the_old_ones(gpu, B, shift):
+    """New states shifted against the old ones in one buffer: the separate
+    kernels have read every old state before they write a new one."""
+    import torch
+    from paper_1605_04809_amd import binding as nb
+    wl = unit_gain(BASE.replace(B=B))
+    g = gpu.GpuRun(wl)
+    want = g.step(wl.s_prev, wl.y_prev, wl.sent_id, wl.req)
+    H, pad = wl.cfg.H, 40
+    buf = torch.zeros((B + 2 * pad, H), device="cuda")
+    old, new = buf[pad:pad + B], buf[pad + shift:pad + shift + B]
+    old.copy_(gpu.cuda(wl.s_prev))
+    lp = torch.empty(B, device="cuda")
+    nb.nmt_score_batch(g.model, g.src, old, gpu.cuda(wl.y_prev), gpu.cuda(wl.sent_id), gpu.cuda(wl.req), lp, new)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(new.cpu().numpy(), want["s_new"])
+    np.testing.assert_array_equal(lp.cpu().numpy(), want["logp"])
+    g.close()
+
+
 def test_keys_beyond_the_factors_range(gpu):
     cfg = BASE.replace(B=40, A=128)
     wl = unit_gain(cfg, key_scale=40.0, query_scale=60.0)
