@@ -2311,6 +2311,7 @@ k_attention_grouped(
                             (int)blockIdx.y * W4, W4);
 }
 
+constexpr int kAttnMaxParts = 16;
 template <int G, int NQ>
 static void attention_grouped(int B, int A, int C, int Tpad, QuerySrc q, const float* kfac, const float* pctx,
                               const int32_t* kbig, const float* ctx, const int32_t* len, const AttnGroups& grp, int S, const float* v, float* c,
@@ -2324,12 +2325,13 @@ static void attention_grouped(int B, int A, int C, int Tpad, QuerySrc q, const f
   // the columns, so that a thread's chain of annotation loads is shorter (12
   // rows: step 78.3 -> 74.8 us).  Each part scores the positions anew: with
   // 125 tiles and more that cost more than it gave (250 tiles in two parts:
-  // ruen step 256 -> 263 us).  Parts are whole waves of float4 columns.
+  // ruen step 256 -> 263 us).  Parts are whole waves of float4 columns: the
+  // largest divisor of the row's waves that leaves every block a CU.
   int parts = 1;
   const int64_t tiles = ceil_div(B, G);
-  if (C4 >= 512 && 8 * tiles <= cus)
-    for (int p : {2, 4, 7, 8, 14})
-      if (C4 % (64 * p) == 0 && p * tiles <= cus) parts = p;
+  if (C4 >= 512 && C4 % 64 == 0 && 8 * tiles <= cus)
+    for (int p = 2; p <= kAttnMaxParts && p * tiles <= cus; ++p)
+      if (C4 / 64 % p == 0) parts = p;
   const int W4 = C4 / parts;
   // Position groups of the context phase: whole waves per group (W4 a
   // multiple of 64), so every wave meets its one barrier.

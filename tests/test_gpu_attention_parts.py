@@ -31,3 +31,21 @@ def test_few_rows_match_the_oracle(wtype, B, S):
         bar = 2e-2 if wtype == "bf16" else 1e-4 if k.startswith("log") else 1e-5
         assert gpu.max_abs(got[k], ref[k]) <= bar, (k, gpu.max_abs(got[k], ref[k]))
     g.close()
+
+
+# 9 to 13 and 16 waves of float4 columns: parts of 9, 10 or 5, 11, 12 or 6, 13 and 16 or 8
+@pytest.mark.parametrize("B", [5, 30])
+@pytest.mark.parametrize("H,E", [(640, 384), (768, 256), (768, 500), (900, 372), (1024, 256), (1200, 496)])
+def test_other_widths_match_the_oracle(B, H, E):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_cases as gpu
+    wl = unit_gain(BASE.replace(B=B, S=2, H=H, E=E, A=256))
+    ann = random_annotations(wl.cfg, seed=85)
+    g, o = gpu.GpuRun(wl, ctx_f32=ann), gpu.OracleRun(wl, ctx_f32=ann)
+    args = (wl.s_prev, wl.y_prev, wl.sent_id, wl.req)
+    got, ref = g.step(*args), o.step(*args)
+    for k in ("s1", "s_new", "t", "c", "logp", "logZ"):
+        assert gpu.max_abs(got[k], ref[k]) <= (1e-4 if k.startswith("log") else 1e-5), k
+    g.close()
