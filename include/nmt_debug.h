@@ -54,8 +54,10 @@ int32_t nmt_debug_precompute(int32_t on);
 
 /* Whether small fp32 models run the step up to the readout as one kernel
  * (1, the default) or as the separate kernels (0), so a test can compare the
- * two, which give the same values.  Process-wide.  Returns the previous
- * setting, or -1 (and changes nothing) for a value other than 0 or 1. */
+ * two, which give the same values (a row whose query is within the keys'
+ * factors but whose neighbour's is not: up to rounding).  Process-wide.
+ * Returns the previous setting, or -1 (and changes nothing) for a value other
+ * than 0 or 1. */
 int32_t nmt_debug_small_step(int32_t on);
 
 /* The encoder's recurrence: one launch where it applies (1, the default), the

@@ -2469,7 +2469,10 @@ hipError_t launch_masked_copy(int S, int Tpad, int C, const float* src, const in
 // 1 to 2 us of work each).  The products use the fp32 tile's MFMA in its
 // order of k (the weights as its row operand, which exchanges a product's
 // factors), the attention its order of terms and positions, so the results
-// are those of the separate kernels bit for bit.  R is the smallest power of
+// are those of the separate kernels bit for bit, but for one case: whether a
+// row's scores take the formula for queries beyond the keys' factors is
+// decided here from its own query, there from the queries of all rows of its
+// tile (both formulas err by a few 1e-7).  R is the smallest power of
 // two that keeps the blocks to one per CU; past 8 rows a block's attention,
 // which reads a row's keys for that row alone, would outlast the grouped
 // kernel's.
