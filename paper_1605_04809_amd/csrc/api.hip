@@ -513,9 +513,9 @@ hipError_t split_weights(nmt_model* m, hipStream_t st) {
   for (int i = 0; i < kItems && fits && e == hipSuccess; ++i) e = pack(all[i], at[i]);
   if (m->out.sp.steps && e == hipSuccess) {
     SplitW& sp = m->out.sp;
-    e = pack(out, at_out);
-    sp.bias = (float*)(base + at_bias);
-    if (e == hipSuccess) e = launch_scaled_bias(m->out, bias_scale, sp.blocks * 32, sp.bias, st);
+    sp.bias = (float*)(base + at_bias);  // right behind the halves
+    e = launch_scaled_bias(m->out, bias_scale, sp.blocks * 32, sp.bias, st);
+    if (e == hipSuccess) e = pack(out, at_out);
   }
   // the recurrence: one scale for both directions
   const int rec_scale =

@@ -212,6 +212,20 @@ def test_the_scale_sees_every_row(gpu, kw, row):
     g.close()
 
 
+# Six 16-k steps of the output weights (E of 65 to 96), whose last thread block packs only in part where the number of
+# column blocks is odd (a write past it would fall on the scaled bias); the vocabulary kernel's row tiles of 32 (70 and
+# 300 rows) and 64, two steps in flight.
+@pytest.mark.parametrize("kw", [dict(E=E, V=V, B=B, H=H, A=64) for E in (68, 80, 96) for V, B, H in
+                                ((1003, 70, 64), (1003, 1100, 256), (2016, 300, 64), (2016, 2100, 256))],
+                         ids=lambda kw: "_".join(f"{k}{v}" for k, v in kw.items()))
+def test_six_vocabulary_steps(gpu, kw):
+    wl = unit_gain(BASE.replace(**kw))
+    g, o = gpu.GpuRun(wl), gpu.OracleRun(wl)
+    args = (wl.s_prev, wl.y_prev, wl.sent_id, wl.req)
+    check(gpu, g.step(*args), o.step(*args), str(kw))
+    g.close()
+
+
 # Batches whose vocabulary takes more slices on the halves than on the fp32 MFMA (256 CUs): their partials over the
 # projections and the query, and (widths of 4) in a region of their own.
 @pytest.mark.parametrize("kw", [dict(B=558, V=13488), dict(B=2275, V=26024), dict(B=40, V=13488, H=4, A=4, E=4),
