@@ -39,8 +39,9 @@ int64_t nmt_debug_alloc_hook(int32_t fail_after);
  * previous form, or -1 (and changes nothing) for a form outside 0..4. */
 int32_t nmt_debug_gemm_form(int32_t form);
 
-/* How many launches of the process took a weight-streaming form (GRU or
- * plain product), so a test can tell which form ran. */
+/* How many launches of the process took a weight-streaming form (GRU or plain
+ * product of a bf16 model, any product of an fp32 model on fp16 halves but
+ * the vocabulary's), so a test can tell which form ran. */
 int64_t nmt_debug_gemm_streamed(void);
 
 /* Whether fp32 models created from now on take the previous word's and the
