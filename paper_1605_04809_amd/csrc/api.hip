@@ -83,52 +83,66 @@ struct Allocs {
 // 50 words at the paper's sizes) took longer than the encoder's kernels: 0.7
 // of 1.0 ms.  A destroyed source, after the wait for the device that it makes
 // anyway, leaves its block here for the model's next one.  Bounded by
-// kPoolBytes; freed with the model, and whenever a device allocation of the
+// kPoolBytes and kPoolBlocks; freed with the model, and whenever a device allocation of the
 // library would fail otherwise.
 constexpr size_t kPoolBytes = (size_t)1 << 30;
+constexpr int kPoolBlocks = 64;
+
+// What a pool lets go of, to be freed outside its lock.  (Fixed arrays, here
+// and below: giving a block back must not throw through the C interface.)
+struct FreedBlocks {
+  void* p[kPoolBlocks + 1];
+  int n = 0;
+  bool free_all() {
+    for (int i = 0; i < n; ++i) (void)hipFree(p[i]);
+    return n > 0;
+  }
+};
 
 struct BlockPool {
+  struct Block {
+    void* p;
+    size_t n;
+  };
   std::mutex mu;
   int device = -1;
   bool closed = false;  // the model is gone: blocks are freed as they come back
-  std::vector<std::pair<void*, size_t>> idle;  // oldest first
+  Block idle[kPoolBlocks];  // oldest first
+  int count = 0;
   size_t idle_bytes = 0;
 
+  Block remove(int i) {
+    const Block b = idle[i];
+    for (--count; i < count; ++i) idle[i] = idle[i + 1];
+    idle_bytes -= b.n;
+    return b;
+  }
   void* take(size_t need, size_t* got) {  // the smallest idle block that holds need without wasting half of itself
     std::lock_guard<std::mutex> lock(mu);
-    size_t best = idle.size();
-    for (size_t i = 0; i < idle.size(); ++i)
-      if (idle[i].second >= need && idle[i].second <= 2 * need + ((size_t)1 << 20) &&
-          (best == idle.size() || idle[i].second < idle[best].second))
+    int best = -1;
+    for (int i = 0; i < count; ++i)
+      if (idle[i].n >= need && idle[i].n <= 2 * need + ((size_t)1 << 20) && (best < 0 || idle[i].n < idle[best].n))
         best = i;
-    if (best == idle.size()) return nullptr;
-    void* p = idle[best].first;
-    *got = idle[best].second;
-    idle_bytes -= idle[best].second;
-    idle.erase(idle.begin() + best);
-    return p;
+    if (best < 0) return nullptr;
+    const Block b = remove(best);
+    *got = b.n;
+    return b.p;
   }
-  // Keeps the block, dropping the oldest ones past the bound; what must be freed is left in out.
-  void put(void* p, size_t n, std::vector<void*>& out) {
+  // Keeps the block, letting the oldest ones past the bounds go.
+  void put(void* p, size_t n, FreedBlocks& out) {
     std::lock_guard<std::mutex> lock(mu);
     if (closed || n > kPoolBytes) {
-      out.push_back(p);
+      out.p[out.n++] = p;
       return;
     }
-    idle.emplace_back(p, n);
+    while (count == kPoolBlocks || (count > 0 && idle_bytes + n > kPoolBytes)) out.p[out.n++] = remove(0).p;
+    idle[count++] = Block{p, n};
     idle_bytes += n;
-    while (idle_bytes > kPoolBytes) {
-      out.push_back(idle.front().first);
-      idle_bytes -= idle.front().second;
-      idle.erase(idle.begin());
-    }
   }
-  void drain(bool close, std::vector<void*>& out) {
+  void drain(bool close, FreedBlocks& out) {
     std::lock_guard<std::mutex> lock(mu);
     closed = closed || close;
-    for (const auto& b : idle) out.push_back(b.first);
-    idle.clear();
-    idle_bytes = 0;
+    while (count > 0) out.p[out.n++] = remove(count - 1).p;
   }
 };
 
@@ -144,23 +158,24 @@ std::shared_ptr<BlockPool> open_pool(int device) {
   return p;
 }
 bool free_idle_blocks() {  // true if anything was freed
-  std::vector<void*> out;
-  {
-    std::lock_guard<std::mutex> lock(g_pools_mu);
-    for (const auto& p : g_pools) p->drain(false, out);
+  bool any = false;
+  std::lock_guard<std::mutex> lock(g_pools_mu);
+  for (const auto& p : g_pools) {
+    FreedBlocks out;
+    p->drain(false, out);
+    any = out.free_all() || any;
   }
-  for (void* p : out) (void)hipFree(p);
-  return !out.empty();
+  return any;
 }
 void close_pool(const std::shared_ptr<BlockPool>& p) {
   if (!p) return;
-  std::vector<void*> out;
   {
     std::lock_guard<std::mutex> lock(g_pools_mu);
     g_pools.erase(std::remove(g_pools.begin(), g_pools.end(), p), g_pools.end());
   }
+  FreedBlocks out;
   p->drain(true, out);
-  for (void* q : out) (void)hipFree(q);
+  out.free_all();
 }
 
 struct GruBias {
@@ -685,9 +700,9 @@ void pooled_free(BlockPool& pool, void* p, size_t n) {
     return;
   }
   --g_live_allocs;
-  std::vector<void*> out;
+  FreedBlocks out;
   pool.put(p, n, out);
-  for (void* q : out) (void)hipFree(q);
+  out.free_all();
 }
 
 nmt_status new_source(nmt_model* m, int32_t S, int32_t Tpad, const int32_t* h_len, bool with_scratch,

@@ -151,3 +151,26 @@ def test_source_blocks_come_back_and_outlive_their_model():
     g.model.close()
     g.src.close()
     assert nb.debug_alloc_hook(-1) == live
+
+
+def test_more_idle_blocks_than_the_pool_keeps():
+    """100 sources of growing size at once, then destroyed and set up again."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_cases
+    from paper_1605_04809_amd import binding as nb
+    live = nb.debug_alloc_hook(-1)
+    wl = unit_gain(BASE.replace(S=1, H=32, Tpad=100, len_hi=100))
+    m = nb.Model.from_workload(wl)
+    ids = gpu_cases.cuda(wl.src_ids)
+    want = {}
+    for turn in range(2):
+        srcs = [(n, nb.nmt_encode(m, ids[:, :n].contiguous(), np.array([n], np.int32))) for n in range(1, 101)]
+        for n, s in srcs:
+            ctx = s.copy_out()[0].cpu().numpy()
+            np.testing.assert_array_equal(ctx, want.setdefault(n, ctx))
+        for _, s in srcs:
+            s.close()
+    m.close()
+    assert nb.debug_alloc_hook(-1) == live

@@ -56,6 +56,17 @@ def test_one_kernel_equals_the_separate_ones(gpu, kw):
     g.close()
 
 
+def test_longest_sentences(gpu):
+    """Eight rows a block with the scores of 1,024 positions: 82 KB of LDS."""
+    wl = unit_gain(BASE.replace(B=1100, H=128, E=256, A=256, S=2, Tpad=1024, len_hi=1024))
+    wl.src_len[0] = 1024
+    g = gpu.GpuRun(wl, ctx_f32=random_annotations(wl.cfg, seed=104))
+    one, apart = both(lambda: g.step(wl.s_prev, wl.y_prev, wl.sent_id, wl.req))
+    for k in apart:
+        np.testing.assert_array_equal(one[k], apart[k], err_msg=k)
+    g.close()
+
+
 @pytest.mark.parametrize("shift", [1, 37, -1, -37])
 @pytest.mark.parametrize("B", [300, 2000])
 def test_new_states_over_a_part_of_the_old_ones(gpu, B, shift):
