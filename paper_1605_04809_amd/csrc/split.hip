@@ -520,6 +520,65 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
   }
 
+  // Rows outside the halves' range: each wave computes its share of K for
+  // them from fp32, 32 k of loads in flight.  (After the sums, the whole of K
+  // to a wave and a load at a time, one such row took a step of 1,000 rows
+  // from 136 to 520 us; 205 now, 278 where every row is one, 231 with every
+  // product on the fp32 MFMA.)
+  bool own[RF];  // this lane's rows: the sums are in their own units
+#pragma unroll
+  for (int i = 0; i < RF; ++i) own[i] = false;
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    const float mx = lanes_max<VPC>(amax[i]);
+    if (sv == 0) row_max[arow + RP * i] = mx;
+  }
+  __syncthreads();  // (the biases are there too)
+  if (nch > 0) {
+#pragma unroll
+    for (int i = 0; i < RF; ++i) {
+      const float mx = row_max[r0 + 32 * i + l32];
+      own[i] = mx >= A.most || (mx > 0.f && mx < A.least);
+      if (__builtin_amdgcn_ballot_w64(own[i]) == 0) continue;
+      constexpr int U = 4;
+      const int ro = row_off(m0 + r0 + 32 * i + l32);
+      const int kw = ((A.K + KS - 1) / KS + 8 * U - 1) / (8 * U) * (8 * U), k_end = min(A.K, (kg + 1) * kw);
+      int64_t n[CF];
+      f32x16 s[CF];
+#pragma unroll
+      for (int f = 0; f < CF; ++f) {
+        const int b = cb0 + f < Pb.blocks ? cb0 + f : 0;
+        n[f] = (int64_t)b * 32 + l32;
+        if constexpr (GRU) {
+          const int u = b / 3 * 32;
+          n[f] = (int64_t)(u / Pb.hb) * 3 * Pb.hb + (b % 3) * Pb.hb + u % Pb.hb + l32;
+        }
+        s[f] = f32x16{};
+      }
+      // (the packed fp32 rows go on to a multiple of 32, so every k0 has 32)
+      for (int k0 = kg * kw; k0 < k_end; k0 += 8 * U) {  // lane half h holds k 4 h .. 4 h + 3 of eight
+        f32x4 x[U], w[U][CF];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k = k0 + 8 * u + 4 * h;
+          x[u] = buf_load(ares, k < A.K ? ro + k * 4 : kNoLoad, 0);
+#pragma unroll
+          for (int f = 0; f < CF; ++f) w[u][f] = Pb.w32[(int64_t)(k0 / 4 + 2 * u + h) * Pb.n32 + n[f]];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int f = 0; f < CF; ++f) s[f] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[u][f][e], x[u][e], s[f], 0, 0, 0);
+      }
+#pragma unroll
+      for (int f = 0; f < CF; ++f)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][f][r] = own[i] ? s[f][r] : acc[i][f][r];
+    }
+  }
+
   // Epilogue.  A wave's sums are NP pieces (row fragment i, columns 8 q + 4 h
   // .. + 3 of each block); each of the KS waves that share them finishes NPK
   // pieces, adding the k groups' sums from LDS in order, one column block at
@@ -533,7 +592,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   // through the dispatch packet in host memory)
   const int row_0 = row_i[0], row_1 = row_i[RF - 1], e0_0 = ext0[0], e0_1 = ext0[RF - 1], e1_0 = ext1[0],
             e1_1 = ext1[RF - 1];
-  auto pick = [](int x0, int x1, int i) { return RF == 1 || i == 0 ? x0 : x1; };
+  const bool own_0 = own[0], own_1 = own[RF - 1];
+  auto pick = [](auto x0, auto x1, int i) { return RF == 1 || i == 0 ? x0 : x1; };
   CellOps cop[GRU ? NB : 1];
   PlainOps pop[GRU ? 1 : NB][GRU ? 1 : CF];
   auto load_ops = [&](int t0) {
@@ -600,52 +660,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
         sum[t][f] = f32x4{acc[i][f][4 * q], acc[i][f][4 * q + 1], acc[i][f][4 * q + 2], acc[i][f][4 * q + 3]};
       }
   }
-#pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    const float mx = lanes_max<VPC>(amax[i]);
-    if (sv == 0) row_max[arow + RP * i] = mx;
-  }
-  __syncthreads();
   if (!busy) return;
 #pragma unroll
-  for (int t = 0; t < NPK; ++t)
+  for (int t = 0; t < NPK; ++t) {
+    const float inv = pick(own_0, own_1, piece_i(t)) ? 1.f : Pb.inv;
 #pragma unroll
-    for (int f = 0; f < CF; ++f) sum[t][f] *= Pb.inv;
-  // rows outside the halves' range: a wave's pieces are of one row fragment, or (KS = 1) of every one
-  constexpr int NI = KS == 1 ? RF : 1, TI = NPK / NI;
-#pragma unroll
-  for (int ii = 0; ii < NI; ++ii) {
-    const int i = piece_i(TI * ii), lrow = r0 + 32 * i + l32;
-    const float mx = row_max[lrow];
-    const bool mine = mx >= A.most || (mx > 0.f && mx < A.least);
-    if (__builtin_amdgcn_ballot_w64(mine) == 0) continue;
-    const int ro = row_off(m0 + lrow);
-    for (int f = 0; f < CF; ++f) {
-      const int b = cb0 + f;
-      if (b >= Pb.blocks) continue;
-      int64_t n = (int64_t)b * 32 + l32;
-      if constexpr (GRU) {
-        const int u = b / 3 * 32;
-        n = (int64_t)(u / Pb.hb) * 3 * Pb.hb + (b % 3) * Pb.hb + u % Pb.hb + l32;
-      }
-      f32x16 s = f32x16{};
-      for (int k = 0; k < A.K; k += 8) {  // lane half h holds k 4 h .. 4 h + 3 of eight
-        const f32x4 x = buf_load(ares, k + 4 * h < A.K ? ro + (k + 4 * h) * 4 : kNoLoad, 0);
-        const f32x4 w = Pb.w32[(int64_t)(k / 4 + h) * Pb.n32 + n];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(w[e], x[e], s, 0, 0, 0);
-      }
-#pragma unroll
-      for (int t = TI * ii; t < TI * (ii + 1); ++t) {
-        const int q = piece_q(t);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float v = q == 0 ? s[e] : (q == 1 ? s[4 + e] : (q == 2 ? s[8 + e] : s[12 + e]));
-#pragma unroll
-          for (int g = 0; g < CF; ++g) sum[t][g][e] = mine && g == f ? v : sum[t][g][e];
-        }
-      }
-    }
+    for (int f = 0; f < CF; ++f) sum[t][f] *= inv;
   }
 
 #pragma unroll
