@@ -829,10 +829,13 @@ hipError_t launch_plain_sp(const SpA& A, const SplitW& W, const PlainEpi& ep, in
 // bias enters as the accumulators' first term, one fp32 MFMA per
 // accumulator (exact, any magnitude; 2 % of the group's MFMA cycles).
 //
-// What bounds it: power.  The matrix cores are busy 88 % of a clock that the
-// chip holds at about 1.45 GHz.  2,000 rows, E = 500, V = 100,000: 1,393 us
-// with fp32 MFMAs, 522 us here (383 TFLOP/s of fp32 products); 1,000 rows and
-// V = 50,000: 136 us.
+// What bounds it: power.  By counters at 2,000 rows, E = 500, V = 100,000 the
+// matrix cores are busy 80 % of the launch, 88 % of the cycles in which a CU
+// holds its block, at a core clock of about 1.55 GHz, where the chip held 2.39
+// under the fp32 MFMA's form (profiles/step_counters_enru_b2000.md).  1,393 us
+// with fp32 MFMAs; here 461 us with weights of sigma 0.01 and 522 us with
+// unit-gain ones (383 TFLOP/s of fp32 products); 1,000 rows and V = 50,000:
+// 136 us.
 constexpr int kSvWaves = 8, kSvFN = 2;
 constexpr int kSvVectors = 9216;  // LDS vectors of the activation tile (144 KB)
 
